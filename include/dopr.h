@@ -162,13 +162,12 @@ typedef struct {
                                block per CU, 256 prefix slots resident;
                                512 at D = 64), 6 = 4 waves x 32 rows, two
                                blocks per CU, 96 slots resident (256 at
-                               D = 64); 8 = the pass kernel: an 8-wave
-                               block (one per CU at D = 128, two at D = 64)
-                               takes a (work item, kv head) unit, keeps a
-                               prefix of up to 256 slots in LDS for all its
-                               passes of 256 rows, and reads the own keys
-                               from a k^ buffer in the workspace (2 Hkv D
-                               bytes per online token) filled by a
+                               D = 64); 8 = the pass kernel: 4-wave blocks
+                               (two per CU at D = 128, three at D = 64) take
+                               (work item, kv head) units of up to 128 rows,
+                               stream their keys through LDS and read the
+                               own keys from a k^ buffer in the workspace
+                               (2 Hkv D bytes per online token) filled by a
                                separate normalise-and-rotate kernel;
                                4 = exact running-max softmax for every row
                                (slower; the reference for the fast path);
@@ -201,7 +200,8 @@ typedef struct {
   int32_t rows_per_item;    /* 0 = automatic.  Else the size, in stacked
                                rows (token x q head of one kv head), of the
                                work items a document's rows are cut into:
-                               a multiple of 32 in [64, 2^20].  Outputs do
+                               a multiple of 32 in [64, 2^20] (the pass
+                               kernel's items hold at most 128).  Outputs do
                                not depend on it (a tuning and test knob).
                                Full-row calls only: must be 0 for
                                dopr_prefix_attn_score (INVALID_ARG).        */
@@ -241,7 +241,10 @@ dopr_status_t dopr_prefix_attn(dopr_store_t st, int32_t layer,
  *     dopr_prefix_attn_workspace gives the size, except that here the
  *     automatic choice (kernel_variant 0) and the self-check variant 5 never
  *     take the pass kernel (8), whose plan grows with every token; variant 8
- *     is run only when asked for and its plan fits;
+ *     is run only when asked for and its plan fits (its work items counted
+ *     with up to 2048 rows and 32 bytes each per kv head; when only the
+ *     128-row items it is run with do not fit, the block kernels run, with
+ *     the same outputs);
  *   - the call allocates nothing: no hipMalloc, hipFree or allocating
  *     library routine.
  * Every call on one device shares that device's scratch: calls that overlap

@@ -27,8 +27,11 @@ TIMERS_LIB = os.path.join(HERE, "libdopr_timers.so")
 SOURCES = ["api.hip", "store.hip", "group.hip", "attn.hip", "stream.hip",
            "score.hip", "layer.hip", "salience.hip"]
 # per-file flags: the streaming kernel's cursor must stay in scalar
-# registers (common-code sinking would move it to scratch memory)
-EXTRA = {"stream.hip": ["-mllvm", "-simplifycfg-sink-common=false"]}
+# registers (common-code sinking would move it to scratch memory), and its
+# claims are atomics whose results are read much later (the wave-wide form
+# the compiler would make of them reads each result at once)
+EXTRA = {"stream.hip": ["-mllvm", "-simplifycfg-sink-common=false",
+                        "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 ARCH = "gfx950"
 
 FLAGS = [

@@ -96,9 +96,9 @@ dopr_status_t layout_store(const dopr_store_desc_t *d, StoreLayout *lay,
 
 bool uses_stream_kernel(int32_t variant, const dopr_store *st);
 
-// Rows per work item: long items for the full layer (the block kernels and
-// the pass kernel stage a document's prefix once per item and walk the item
-// in passes), and 32 for the one-wave-per-unit score kernel that the
+// Rows per work item: long items for the block kernels (they stage a
+// document's prefix once per item and walk the item in passes; the pass
+// kernel's items are cut to kPassRows by check_attn), and 32 for the one-wave-per-unit score kernel that the
 // automatic choice takes when every prefix is at most kScoreRowsMaxLen
 // slots.
 int32_t default_rows_per_item(int32_t variant, bool score_only,
@@ -172,6 +172,9 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
       a->rows_per_item ? a->rows_per_item
                        : default_rows_per_item(a->kernel_variant, score_only,
                                                st->max_len, *n_rep);
+  shape->stream = !score_only && uses_stream_kernel(a->kernel_variant, st);
+  if (shape->stream && shape->rows_per_item > kPassRows)
+    shape->rows_per_item = kPassRows;
   // work units (item, kv head) are numbered in 32 bits by the scheduler's
   // queues: the plan's item capacity times the kv heads must stay below
   // 2^31
@@ -189,7 +192,6 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
   shape->n_kv_heads = st->n_kv_heads;
   shape->head_dim = st->head_dim;
   shape->score_only = score_only;
-  shape->stream = !score_only && uses_stream_kernel(a->kernel_variant, st);
   return DOPR_OK;
 }
 
@@ -377,6 +379,42 @@ dopr_status_t scratch_ptr(int dev, void **out) {
   return DOPR_OK;
 }
 
+dopr_status_t noalloc_too_large(size_t need) {
+  return fail(DOPR_ERR_WORKSPACE,
+              "the call needs " + std::to_string(need) +
+                  " bytes of scratch; the no-alloc entry point holds " +
+                  std::to_string(kNoAllocScratchBytes) +
+                  " (use dopr_prefix_attn with a workspace)");
+}
+
+// The plan of a no-alloc call.  The block kernels, unless the pass kernel is
+// asked for and its plan fits.  Whether a call is accepted does not depend
+// on how finely the pass kernel cuts its items: its size counts as the block
+// plan's (items of 2048 rows unless the caller sets them), k^ of every token
+// and 32 bytes per work unit; a call within the limit whose plan of
+// 128-row items is beyond it runs the block kernels, which give the same
+// bits.
+dopr_status_t noalloc_shape(const dopr_attn_args_t *a, PlanShape *shape) {
+  if (!shape->stream) return DOPR_OK;
+  PlanShape block = *shape;
+  block.stream = false;
+  block.rows_per_item = a->rows_per_item ? a->rows_per_item : 2048;
+  if (a->kernel_variant == 8) {
+    const int64_t rows = a->total_tokens * shape->n_rep;
+    const int64_t cap = a->n_pairs + (rows + block.rows_per_item - 1) /
+                                         block.rows_per_item + 1;
+    const size_t need =
+        plan_bytes(block) +
+        align_up(2 * (size_t)a->total_tokens * shape->n_kv_heads *
+                     shape->head_dim, kAlign) +
+        align_up(32 * (size_t)cap * shape->n_kv_heads, kAlign);
+    if (need > kNoAllocScratchBytes) return noalloc_too_large(need);
+    if (plan_bytes(*shape) <= kNoAllocScratchBytes) return DOPR_OK;
+  }
+  *shape = block;
+  return DOPR_OK;
+}
+
 // The attention call in both modes: every online row (head == NULL) or the
 // score token's rows with the fused score head.  no_alloc: the plan goes to
 // the library's scratch array instead of the caller's workspace; the
@@ -396,7 +434,8 @@ dopr_status_t run_attention(dopr_store_t st, int32_t layer,
       return fail(DOPR_ERR_INVALID_ARG,
                   "workspace must be NULL with 0 bytes: the no-alloc call "
                   "uses the library's scratch");
-    shape.stream = a->kernel_variant == 8;
+    s = noalloc_shape(a, &shape);
+    if (s != DOPR_OK) return s;
   }
   if (layer < 0 || layer >= st->n_layers)
     return fail(DOPR_ERR_INVALID_ARG, "layer out of range");
@@ -428,12 +467,7 @@ dopr_status_t run_attention(dopr_store_t st, int32_t layer,
   const size_t need = plan_bytes(shape);
   void *ws = a->workspace;
   if (no_alloc) {
-    if (need > kNoAllocScratchBytes)
-      return fail(DOPR_ERR_WORKSPACE,
-                  "the call needs " + std::to_string(need) +
-                      " bytes of scratch; the no-alloc entry point holds " +
-                      std::to_string(kNoAllocScratchBytes) +
-                      " (use dopr_prefix_attn with a workspace)");
+    if (need > kNoAllocScratchBytes) return noalloc_too_large(need);
   } else {
     if (reinterpret_cast<uintptr_t>(a->workspace) % kAlign)
       return fail(DOPR_ERR_INVALID_ARG, "workspace must be 256-byte aligned");

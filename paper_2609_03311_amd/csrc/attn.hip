@@ -969,7 +969,7 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   // kernels for score rows (1, 3 and 8 map to 6).
   const int D = st.head_dim;
   int shape_v = a->kernel_variant;
-  if (shape_v == 0 || shape_v == 5)
+  if (shape_v == 0 || shape_v == 5 || (shape_v == 8 && !score && !pl.kh))
     shape_v = score ? (st.max_len <= kScoreRowsMaxLen ? 7 : 6)
               : pl.kh ? 8
               : st.max_len <= small_chunks(D) * KC ? 6
@@ -977,7 +977,6 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   static_assert(small_chunks(128) * KC == kShortPrefix128,
                 "short prefixes are those two blocks per CU keep resident");
   if (score && (shape_v == 1 || shape_v == 3 || shape_v >= 8)) shape_v = 6;
-  if (shape_v >= 8 && !pl.kh) return hipErrorInvalidValue;
   e = D == 128 ? launch_passes<128>(p, kp, a->n_pairs, shape_v, score, s)
                : launch_passes<64>(p, kp, a->n_pairs, shape_v, score, s);
   if (e != hipSuccess) return e;

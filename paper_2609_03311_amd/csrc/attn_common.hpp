@@ -41,7 +41,7 @@ struct AttnParams {
   // pass kernel: precomputed own keys k^ [Hkv][Ntok][D], a zero page and
   // the work-unit table
   const uint16_t *kh, *zero;
-  const int4 *units;
+  const PassUnit *units;
   int64_t ntok;
   // work units of each queue, costliest first (see unit_at)
   const int32_t *qorder;
@@ -206,72 +206,16 @@ __device__ __forceinline__ int find_pair(const AttnParams &P, int r) {
 // stays packed until the norm is known; the rotation then runs one k-step
 // pair at a time, each finished fragment pinned in place so the compiler
 // does not keep the step's inputs alive until the first product.
-template <int D>
-__device__ __forceinline__ void q_fragments(const uint16_t *qrow,
-                                            const uint16_t *w,
-                                            const float2 *rope_row, int hf,
-                                            float eps, float c, bool norm,
-                                            bf16x8 *qf) {
-  constexpr int NS = D / 16, HS = NS / 2;
-  // every load is issued up front (one round trip to memory): the raw row,
-  // the gains (packed) and this lane's D/4 (cos, sin) pairs
-  uint4 raw[NS], wr[NS];
-  float4 cs[4 * HS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    raw[s] = *reinterpret_cast<const uint4 *>(qrow + 16 * s + 8 * hf);
-  w += opaque_zero();
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    wr[s] = *reinterpret_cast<const uint4 *>(w + 16 * s + 8 * hf);
-#pragma unroll
-  for (int s = 0; s < HS; ++s)
-#pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2)
-      cs[4 * s + e2] =
-          reinterpret_cast<const float4 *>(rope_row + 16 * s + 8 * hf)[e2];
-  // sum of squares straight from the packed pairs (v_dot2), so the
-  // unpacked row is not kept alive until the rotation
-  float ss = 0.f;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) ss = sumsq8(raw[s], ss);
-  ss += __shfl_xor(ss, 32, 64);
-  const float inv = norm ? c * rsqrtf(ss * (1.0f / D) + eps) : c;
-#pragma unroll
-  for (int s = 0; s < HS; ++s) {
-    float x0[8], x1[8], w0[8], w1[8];
-    unpack8(raw[s], x0);
-    unpack8(raw[s + HS], x1);
-    unpack8(wr[s], w0);
-    unpack8(wr[s + HS], w1);
-#pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      const float4 t = cs[4 * s + e2];  // (cos, sin) of dims 2e2, 2e2 + 1
-      const int e = 2 * e2;
-      float a = x0[e] * (inv * w0[e]), b = x1[e] * (inv * w1[e]);
-      x0[e] = fmaf(a, t.x, -b * t.y);
-      x1[e] = fmaf(b, t.x, a * t.y);
-      a = x0[e + 1] * (inv * w0[e + 1]);
-      b = x1[e + 1] * (inv * w1[e + 1]);
-      x0[e + 1] = fmaf(a, t.z, -b * t.w);
-      x1[e + 1] = fmaf(b, t.z, a * t.w);
-    }
-    qf[s] = to_bf16x8(x0);
-    qf[s + HS] = to_bf16x8(x1);
-    pin(qf[s]);
-    pin(qf[s + HS]);
-  }
-}
-
-// ---- q^ with the rotary pairs and gains shared across a token's lanes ----
+//
+// ---- the rotary pairs and gains shared across a token's lanes ----
 // When n_rep is a multiple of 4 (of 2), the four lanes of a quad (the two
 // lanes of a pair) hold query heads of one token and the same half of the
 // head dims, so they need the same (cos, sin) pairs and gains.  Each lane
 // loads its share; the multiplies that use a value read it from the owning
 // lane through a DPP broadcast within the quad folded into the instruction
 // (the compiler's DPP moves are not folded into these users, so the
-// operations are written out).  Every product and sum is the one
-// q_fragments forms, in the same order and rounding: fma(cos, a, sin * -b)
+// operations are written out).  Every product and sum is the one that the
+// unshared form makes, in the same order and rounding: fma(cos, a, sin * -b)
 // and fma(cos, b, sin * a).  s_nop 4 covers the wait states a DPP read
 // needs after a vector write of its source or of EXEC.
 //
@@ -372,48 +316,61 @@ __device__ __forceinline__ void unpack8_at(int k, const uint4 &u,
   }
 }
 
-// q_fragments with the sharing above among GROUP = 4 or 2 lanes; qk = the
+// q^ with the sharing above among GROUP = 4 or 2 lanes (1: none); qk = the
 // lane's place in its group.  Lane qk loads gain vectors s = qk*NS/GROUP ..
 // + NS/GROUP - 1 and, of every k-step pair s, the rotary float4s
-// e2 = qk*4/GROUP .. + 4/GROUP - 1 (q_fragments' numbering), so the
-// group's loads of one k-step cover contiguous bytes of the row.
+// e2 = qk*4/GROUP .. + 4/GROUP - 1, so the
+// group's loads of one k-step cover contiguous bytes of the row.  In two
+// steps: the loads of a row, and q^ from the loaded row (the pass kernel
+// issues the loads one pass ahead).
 template <int D, int GROUP>
-__device__ __forceinline__ void q_fragments_shared(const uint16_t *qrow,
-                                                   const uint16_t *w,
-                                                   const float2 *rope_row,
-                                                   int hf, int qk, float eps,
-                                                   float c, bool norm,
-                                                   bf16x8 *qf) {
-  constexpr int NS = D / 16, HS = NS / 2, GW = NS / GROUP, EW = 4 / GROUP;
-  constexpr int BASE = GROUP == 4 ? 0 : 4;  // source codes of the group
-  uint4 raw[NS], wr[GW];
+struct QRow {
+  static constexpr int NS = D / 16, HS = NS / 2, EW = 4 / GROUP;
+  uint4 raw[NS];
   float4 cs[HS * EW];
+};
+
+template <int D, int GROUP>
+__device__ __forceinline__ void q_row_load(const uint16_t *qrow,
+                                           const float2 *rope_row, int hf,
+                                           int qk, QRow<D, GROUP> &q) {
+  using Q = QRow<D, GROUP>;
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
-    raw[s] = *reinterpret_cast<const uint4 *>(qrow + 16 * s + 8 * hf);
-  w += opaque_zero();
+  for (int s = 0; s < Q::NS; ++s)
+    q.raw[s] = *reinterpret_cast<const uint4 *>(qrow + 16 * s + 8 * hf);
 #pragma unroll
-  for (int m = 0; m < GW; ++m)
-    wr[m] = *reinterpret_cast<const uint4 *>(w + 16 * (qk * GW + m) + 8 * hf);
+  for (int s = 0; s < Q::HS; ++s)
 #pragma unroll
-  for (int s = 0; s < HS; ++s)
-#pragma unroll
-    for (int m = 0; m < EW; ++m)
-      cs[s * EW + m] = reinterpret_cast<const float4 *>(
-          rope_row + 16 * s + 8 * hf)[qk * EW + m];
+    for (int m = 0; m < Q::EW; ++m)
+      q.cs[s * Q::EW + m] = reinterpret_cast<const float4 *>(
+          rope_row + 16 * s + 8 * hf)[qk * Q::EW + m];
+}
+
+template <int D, int GROUP>
+__device__ __forceinline__ void q_row_form(const QRow<D, GROUP> &q,
+                                           const uint4 *wr, float eps,
+                                           float c, bool norm, bf16x8 *qf) {
+  using Q = QRow<D, GROUP>;
+  constexpr int NS = Q::NS, HS = Q::HS, GW = NS / GROUP, EW = Q::EW;
+  constexpr int BASE = GROUP == 4 ? 0 : 4;  // source codes of the group
   float ss = 0.f;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) ss = sumsq8(raw[s], ss);
+  for (int s = 0; s < NS; ++s) ss = sumsq8(q.raw[s], ss);
   ss += __shfl_xor(ss, 32, 64);
   const float inv = norm ? c * rsqrtf(ss * (1.0f / D) + eps) : c;
   const uint32_t c16 = 65536u + opaque_zero(), hi = 0xffff0000u + opaque_zero();
 #pragma unroll
   for (int s = 0; s < HS; ++s) {
     float x0[8], x1[8], w0[8], w1[8];
-    unpack8(raw[s], x0);
-    unpack8(raw[s + HS], x1);
-    unpack8_at(BASE + s / GW, wr[s % GW], c16, hi, w0);
-    unpack8_at(BASE + (s + HS) / GW, wr[(s + HS) % GW], c16, hi, w1);
+    unpack8(q.raw[s], x0);
+    unpack8(q.raw[s + HS], x1);
+    if constexpr (GROUP == 1) {
+      unpack8(wr[s], w0);
+      unpack8(wr[s + HS], w1);
+    } else {
+      unpack8_at(BASE + s / GW, wr[s % GW], c16, hi, w0);
+      unpack8_at(BASE + (s + HS) / GW, wr[(s + HS) % GW], c16, hi, w1);
+    }
 #pragma unroll
     for (int e2 = 0; e2 < 4; ++e2) {
       const int e = 2 * e2;
@@ -421,8 +378,16 @@ __device__ __forceinline__ void q_fragments_shared(const uint16_t *qrow,
       const float b0 = x1[e] * (inv * w1[e]);
       const float a1 = x0[e + 1] * (inv * w0[e + 1]);
       const float b1 = x1[e + 1] * (inv * w1[e + 1]);
-      rot_pairs_at(BASE + e2 / EW, cs[s * EW + e2 % EW], a0, b0, a1, b1,
-                   x0[e], x1[e], x0[e + 1], x1[e + 1]);
+      const float4 t = q.cs[s * EW + e2 % EW];
+      if constexpr (GROUP == 1) {
+        x0[e] = fmaf(a0, t.x, -b0 * t.y);
+        x1[e] = fmaf(b0, t.x, a0 * t.y);
+        x0[e + 1] = fmaf(a1, t.z, -b1 * t.w);
+        x1[e + 1] = fmaf(b1, t.z, a1 * t.w);
+      } else {
+        rot_pairs_at(BASE + e2 / EW, t, a0, b0, a1, b1, x0[e], x1[e],
+                     x0[e + 1], x1[e + 1]);
+      }
     }
     qf[s] = to_bf16x8(x0);
     qf[s + HS] = to_bf16x8(x1);
@@ -431,8 +396,26 @@ __device__ __forceinline__ void q_fragments_shared(const uint16_t *qrow,
   }
 }
 
+template <int D, int GROUP>
+__device__ __forceinline__ void q_fragments(const uint16_t *qrow,
+                                                   const uint16_t *w,
+                                                   const float2 *rope_row,
+                                                   int hf, int qk, float eps,
+                                                   float c, bool norm,
+                                                   bf16x8 *qf) {
+  constexpr int GW = D / 16 / GROUP;
+  QRow<D, GROUP> q;
+  uint4 wr[GW];
+  w += opaque_zero();
+#pragma unroll
+  for (int m = 0; m < GW; ++m)
+    wr[m] = *reinterpret_cast<const uint4 *>(w + 16 * (qk * GW + m) + 8 * hf);
+  q_row_load<D, GROUP>(qrow, rope_row, hf, qk, q);
+  q_row_form<D, GROUP>(q, wr, eps, c, norm, qf);
+}
+
 // q^ for a lane whose token is shared by the lanes of its quad (n_rep a
-// multiple of 4) or pair (n_rep even), else q_fragments.
+// multiple of 4) or pair (n_rep even), else unshared.
 template <int D>
 __device__ __forceinline__ void q_fragments_any(const uint16_t *qrow,
                                                 const uint16_t *w,
@@ -441,13 +424,11 @@ __device__ __forceinline__ void q_fragments_any(const uint16_t *qrow,
                                                 float c, bool norm,
                                                 bf16x8 *qf) {
   if ((n_rep & 3) == 0)
-    q_fragments_shared<D, 4>(qrow, w, rope_row, hf, lane & 3, eps, c, norm,
-                             qf);
+    q_fragments<D, 4>(qrow, w, rope_row, hf, lane & 3, eps, c, norm, qf);
   else if ((n_rep & 1) == 0)
-    q_fragments_shared<D, 2>(qrow, w, rope_row, hf, lane & 1, eps, c, norm,
-                             qf);
+    q_fragments<D, 2>(qrow, w, rope_row, hf, lane & 1, eps, c, norm, qf);
   else
-    q_fragments<D>(qrow, w, rope_row, hf, eps, c, norm, qf);
+    q_fragments<D, 1>(qrow, w, rope_row, hf, 0, eps, c, norm, qf);
 }
 #undef DPP_UNPACK
 #undef DPP_ROT
@@ -750,13 +731,13 @@ __device__ __forceinline__ void qk_part(const uint16_t *kblk,
   }
 }
 
-// V^T fragments f0 .. f0 + RA - 1 of a chunk, f = (db, t).
-template <int D>
+// V^T fragments f0 .. f0 + N - 1 of a chunk, f = (db, t).
+template <int D, int N = RA>
 __device__ __forceinline__ void v_read(const uint16_t *vblk,
                                        const Frag<D> &fo, int f0,
                                        bf16x8 *vf) {
 #pragma unroll
-  for (int f = f0; f < f0 + RA; ++f)
+  for (int f = f0; f < f0 + N; ++f)
     vf[f - f0] = *reinterpret_cast<const bf16x8 *>(
         vblk + (f >> 1) * (32 * KC) + fo.v[f & 1]);
 }

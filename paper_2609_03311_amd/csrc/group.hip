@@ -455,10 +455,10 @@ __global__ __launch_bounds__(128) void k_norm_bound(const uint16_t *kw,
 // and first pair, the document's prefix length and the element offsets of
 // its K and V^T slices for this layer and head; a unit whose logits the
 // norm bounds cannot keep within the reference-free range (the kernels'
-// kNoRefBound) is marked with L = -1 and left to the exact pass.
+// kNoRefBound) is marked by its pair's sign bit and left to the exact pass.
 __global__ __launch_bounds__(kThreads) void k_unit_table(
     Plan pl, StoreView sv, int32_t layer, float c, float no_ref_bound,
-    const int64_t *totals) {
+    int32_t n_rep, int64_t ntok, const uint16_t *v, const int64_t *totals) {
   const int64_t w = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t n_items = totals[kTotItems] < pl.items_cap
                               ? totals[kTotItems]
@@ -466,19 +466,41 @@ __global__ __launch_bounds__(kThreads) void k_unit_table(
   if (w >= n_items * sv.n_kv_heads) return;
   const int32_t item = (int32_t)(w / sv.n_kv_heads);
   const int32_t g = (int32_t)(w % sv.n_kv_heads);
+  const int D = sv.head_dim;
   const int4 it = pl.items[item];
   const int32_t doc = pl.group_doc[it.x];
   const int32_t L = sv.doc_len[doc];
   const int64_t blk = sv.doc_off[doc];
+  const int4 sp = pl.spair[it.w];
   const float kb = fmaxf(
       pl.kown[0],
       sv.kmax[((int64_t)doc * sv.n_layers + layer) * sv.n_kv_heads + g]);
   const bool over = c * pl.kown[1] * kb * 1.001f > no_ref_bound;
-  const int64_t ko = k_offset(blk, L, sv.n_kv_heads, layer, g, sv.head_dim);
-  const int64_t vo = vt_offset(blk, L, sv.n_kv_heads, layer, g, sv.head_dim);
-  pl.units[2 * w] = make_int4(it.y, it.z, it.w, over ? -1 : L);
-  pl.units[2 * w + 1] = make_int4((int32_t)(uint32_t)ko, (int32_t)(ko >> 32),
-                                  (int32_t)(uint32_t)vo, (int32_t)(vo >> 32));
+  union {
+    PassUnit u;
+    int4 q[4];
+  } r;
+  auto put = [](int32_t *to, const uint16_t *p) {
+    to[0] = (int32_t)(uint32_t)(uint64_t)p;
+    to[1] = (int32_t)((uint64_t)p >> 32);
+  };
+  r.u.u0 = it.y / n_rep;
+  r.u.rows = (it.z - it.y) | (it.y - r.u.u0 * n_rep) << 8;
+  r.u.s = over ? it.w | INT32_MIN : it.w;
+  r.u.L = L;
+  put(r.u.k, sv.payload + k_offset(blk, L, sv.n_kv_heads, layer, g, D));
+  put(r.u.vt, sv.payload + vt_offset(blk, L, sv.n_kv_heads, layer, g, D));
+  put(r.u.own_k, pl.kh + (g * ntok + sp.x) * D);
+  put(r.u.own_v, v + ((int64_t)sp.x * sv.n_kv_heads + g) * D);
+  r.u.tok0 = sp.x;
+  r.u.T = sp.y;
+  // (positions are stacked latest first: the item's latest position of its
+  // first pair is at its first row)
+  r.u.jmax = sp.y - 1 - (it.y - sp.z) / n_rep;
+  r.u.g = g;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    reinterpret_cast<int4 *>(pl.units + w)[i] = r.q[i];
 }
 
 // Step 5f: the longest-first order of the work-unit queues.  Unit w =
@@ -642,10 +664,7 @@ Plan carve(void *ws, const PlanShape &s, size_t *bytes) {
   pl.kh = s.stream ? c.take<uint16_t>(s.total_tokens * s.n_kv_heads *
                                       s.head_dim)
                    : nullptr;
-  pl.units = s.stream ? c.take<int4>(cap * 2 * (s.n_kv_heads > 0
-                                                    ? s.n_kv_heads
-                                                    : 1))
-                      : nullptr;
+  pl.units = s.stream ? c.take<PassUnit>(cap * hkv) : nullptr;
   *bytes = c.off;
   return pl;
 }
@@ -676,7 +695,7 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
   PlanArgs pa{a->doc_ids,        a->cu_seqlens,      c.st->d_len,
               c.st->n_docs,      a->total_tokens,    a->n_pairs,
               c.n_rep,           a->max_tokens,      shape.rows_per_item,
-              c.st->d_status,    shape.score_only, false};
+              c.st->d_status,    shape.score_only, shape.stream};
   int64_t *totals = plan_totals(pl);
   const int64_t P = a->n_pairs;
   const int64_t init_n = c.st->n_docs > kCounters ? c.st->n_docs : kCounters;
@@ -733,7 +752,8 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
     hipLaunchKernelGGL(k_unit_table, dim3(blocks_for(n_units, kThreads)),
                        dim3(kThreads), 0, s, pl, c.st->view(), c.layer,
                        a->softmax_scale * 1.4426950408889634f, kNoRefBound,
-                       totals);
+                       c.n_rep, a->total_tokens,
+                       static_cast<const uint16_t *>(a->v), totals);
   }
   const double log_theta = std::log((double)a->rope_theta);
   hipLaunchKernelGGL(k_rope_table,

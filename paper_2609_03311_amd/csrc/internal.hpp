@@ -31,6 +31,10 @@ constexpr size_t kNoAllocScratchBytes = DOPR_NOALLOC_SCRATCH_BYTES;
 // 4-wave blocks per CU (96 slots resident each) instead of the pass kernel.
 constexpr int32_t kShortPrefix128 = 96;
 
+// Stacked rows of a work unit of the pass kernel: a 32-row tile for each of
+// a block's four waves.
+constexpr int32_t kPassRows = 128;
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 __host__ __device__ inline int32_t pad8(int32_t n) { return (n + 7) & ~7; }
 
@@ -146,6 +150,23 @@ __device__ __forceinline__ int unit_at32(const int32_t *qorder, int queue,
   return qorder[start + slot];
 }
 
+// A work unit of the pass kernel (one item for one kv head), 64 bytes.
+// Addresses are (low, high) words.
+struct PassUnit {
+  int32_t u0;        // stacked token of its first row
+  int32_t rows;      // rows (at most 128) | first row's head in the group << 8
+  int32_t s;         // first sorted pair; sign bit: over the logit bound
+  int32_t L;         // prefix slots
+  int32_t k[2];      // the document's K slice (this layer and head)
+  int32_t vt[2];     // its V^T slice
+  int32_t own_k[2];  // k^ of the first pair's first token (this head)
+  int32_t own_v[2];  // its v
+  int32_t tok0, T;   // the first pair's first token and token count
+  int32_t jmax;      // its latest position in the unit
+  int32_t g;         // kv head
+};
+static_assert(sizeof(PassUnit) == 64, "one 16-word scalar load");
+
 // Per-call plan built on the device by the grouping kernels (workspace).
 enum Counter {
   kCntValid = 0,     // pairs with a valid, resident document
@@ -190,9 +211,7 @@ struct Plan {
   uint16_t *unit_w;     // [D] bf16 ones: the gains when there is no QK-norm
   float2 *rope;         // [rope_pos][D/2] (cos, sin)
   uint16_t *kh;         // [Hkv][Ntok][D] own keys k^ (pass kernel), or NULL
-  int4 *units;          // [items_cap * Hkv][2] work units (pass kernel):
-                        // (row0, row1, first pair, L or -1 when over the
-                        // logit bound), (K offset lo, hi, V^T offset lo, hi)
+  PassUnit *units;      // [items_cap * Hkv] work units (pass kernel)
   uint16_t *zero;       // 256 zero bytes (streaming kernel loads past row ends)
   int32_t items_cap;
   int32_t blk_cap;

@@ -6,10 +6,10 @@
 Runs the full-layer attention of a synthetic workload (the pass kernel,
 ``kernel_variant`` 8) on libdopr_timers.so, the library built with the pass
 kernel's per-phase cycle counters compiled in, and prints a summary: for
-each wave of the 8-wave block, the share of its cycles in each phase
-(hand-over, prefix staging, pair search, own-chunk loads, q^ prologue,
-waits and barriers, prefix and own products, output), the number of units
-and passes, and the share of the near-empty passes (at most 32 rows).  The
+each wave of a block, the share of its cycles in each phase (q^ prologue,
+waits and barriers, loads issued, prefix and own products, output), the
+number of units (passes of up to 128 rows) and of key batches, and the share
+of the near-empty passes (at most 32 rows).  The
 counters are ``s_memtime`` cycles read by every wave at the phase marks;
 the marks themselves cost a few percent, so the step time printed is the
 instrumented kernel's, not the product's.
@@ -26,13 +26,12 @@ import numpy as np
 import paper_2609_03311_amd as pkg
 from paper_2609_03311_amd import _build, profiling
 
-PHASES = ["unit hand-over", "prefix loads issued", "pair search",
-          "own loads issued", "q rows + q^ prologue", "wait for loads",
-          "barrier before products", "prefix chunks", "own chunks: products",
-          "own chunks: barriers", "own chunks: next loads", "epilogue (O, LSE)",
-          "barrier at pass end", "next unit claim"]
-N_SLOTS = 18  # the kernel's kPtSlots: the phases, then the counts
-UNITS, PASSES, TAIL_CYC, TAILS = 14, 15, 16, 17
+PHASES = ["q rows + q^ prologue", "wait and barrier", "next loads issued",
+          "prefix keys: products", "own keys: products", "next rows asked for",
+          "epilogue (O, LSE)"]
+N_SLOTS = 11  # the kernel's kPtSlots: the phases, then the counts
+UNITS, PASSES, TAIL_CYC, TAILS = 7, 8, 9, 10  # PASSES counts key batches
+N_WAVES = 4
 
 
 def run(config: str, steps: int):
@@ -67,7 +66,7 @@ def run(config: str, steps: int):
     read = L.dopr_pass_phase_read
     read.argtypes = [ctypes.POINTER(ctypes.c_ulonglong), ctypes.c_int]
     read.restype = ctypes.c_int
-    buf = (ctypes.c_ulonglong * (8 * N_SLOTS))()
+    buf = (ctypes.c_ulonglong * (N_WAVES * N_SLOTS))()
     once()
     torch.cuda.synchronize()
     if read(buf, 1) != 0:
@@ -81,7 +80,7 @@ def run(config: str, steps: int):
     torch.cuda.synchronize()
     if read(buf, 1) != 0:
         raise SystemExit("dopr_pass_phase_read failed")
-    t = np.array(list(buf), dtype=np.float64).reshape(8, N_SLOTS)
+    t = np.array(list(buf), dtype=np.float64).reshape(N_WAVES, N_SLOTS)
     return t, a.elapsed_time(b) / steps
 
 
@@ -93,19 +92,20 @@ def summary(config: str, steps: int, t, ms: float, command: str) -> str:
            f"kernel_source_sha: {profiling.kernel_source_sha()}",
            f"workload: {config}, {steps} steps, kernel_variant 8",
            f"instrumented step: {ms:.3f} ms (attention + grouping)",
-           f"units per step: {t[0, UNITS] / steps:.0f}, passes per step: "
+           f"units per step: {t[0, UNITS] / steps:.0f}, key batches per step: "
            f"{t[0, PASSES] / steps:.0f} "
            f"({t[0, PASSES] / max(t[0, UNITS], 1):.2f} per unit)",
-           f"cycles per pass (wave 0): {tot[0] / max(t[0, PASSES], 1):.0f}",
+           f"cycles per unit (wave 0): {tot[0] / max(t[0, UNITS], 1):.0f}",
            f"passes of at most 32 rows: {t[0, TAILS] / steps:.0f} per step, "
            f"{t[0, TAIL_CYC] / max(t[0, TAILS], 1):.0f} cycles each, "
            f"{100 * t[0, TAIL_CYC] / tot[0]:.1f} % of wave 0's cycles", "",
-           f"{'phase':<26}" + "".join(f"{'w' + str(w):>8}" for w in range(8))
+           f"{'phase':<26}" + "".join(f"{'w' + str(w):>8}"
+                                      for w in range(len(t)))
            + f"{'mean':>8}"]
     share = 100 * cyc / tot[:, None]
     for i, name in enumerate(PHASES):
         out.append(f"{name:<26}" + "".join(f"{share[w, i]:7.2f}%"
-                                           for w in range(8))
+                                           for w in range(len(t)))
                    + f"{share[:, i].mean():7.2f}%")
     return "\n".join(out) + "\n"
 

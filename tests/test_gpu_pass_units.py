@@ -1,0 +1,85 @@
+"""The pass kernel's work units (128 stacked rows, keys in batches of two
+32-key chunks) at the sizes where they can go wrong: token counts and prefix
+lengths around a chunk, a batch and a unit, one-token pairs, every way the
+lanes share a token's rotary pairs, and non-finite values next to masked
+keys.  Each row's sums are formed in the block kernels' order, so the outputs
+must be bitwise those of variant 2."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_harness import compare, run, setup
+
+pytestmark = pytest.mark.gpu
+
+TOKENS = [1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160]
+SLOTS = [0, 1, 7, 8, 31, 32, 33, 63, 64, 65, 96, 97, 256, 257]
+
+
+def _outputs(case, variant):
+    import torch
+    from paper_2609_03311_amd import pipeline
+    st, o, p = case.st, case.online, case.prm
+    step = pipeline.OnlineStep(case.store, n_pairs=st.n_pairs,
+                               n_q_heads=st.n_q_heads,
+                               total_tokens=st.n_tokens,
+                               max_tokens=int(st.seqlens.max()),
+                               kernel_variant=variant, with_lse=True)
+    step.out.fill_(float("nan"))
+    step.attention(0, case.doc_ids, case.cu, o["q"], o["k"], o["v"],
+                   p["q_norm_w"], p["k_norm_w"])
+    torch.cuda.synchronize()
+    return step.out, step.lse
+
+
+@pytest.mark.parametrize("n_rep,d", [(1, 128), (2, 128), (3, 128), (4, 128),
+                                     (8, 128), (1, 64), (2, 64), (4, 64)])
+def test_units_match_the_block_kernel(n_rep, d):
+    import torch
+    rng = np.random.default_rng(100 * n_rep + d)
+    lens = np.array(SLOTS + [-1], np.int32)
+    # every length with two to four pairs of random token counts, then a
+    # document with many one-token pairs, and two pairs without a document
+    ids = np.concatenate([np.repeat(np.arange(len(SLOTS)),
+                                    rng.integers(2, 5, len(SLOTS))),
+                          np.full(150, 4), [len(SLOTS), len(SLOTS)]])
+    toks = rng.choice(TOKENS, len(ids))
+    toks[-152:-2] = 1
+    order = rng.permutation(len(ids))
+    st = workloads.custom(lens, ids[order], toks[order], 2 * n_rep, 2,
+                          name=f"units_{n_rep}_{d}", head_dim=d)
+    case = setup(st, seed=9, kernel_variant=8)
+    assert run(case) != 0  # the pairs without a document are reported
+    ok = np.nonzero(st.doc_ids != len(SLOTS))[0]
+    compare(case, ok[:24])
+    out8, lse8 = _outputs(case, 8)
+    out2, lse2 = _outputs(case, 2)
+    assert torch.equal(out8.view(torch.int16), out2.view(torch.int16))
+    assert torch.equal(lse8, lse2)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_non_finite_values_stay_with_their_pair(d):
+    """Infinite values in the v of a document's only pair: the rows of other
+    documents keep their bits (a chunk's rows past its pair's end are read as
+    zeros, not as the next pair's values)."""
+    import torch
+    lens = np.array([33, 40, 5], np.int32)
+    ids = np.array([0, 0, 1, 0, 2, 2], np.int32)
+    toks = np.array([33, 40, 65, 7, 1, 129], np.int32)
+    st = workloads.custom(lens, ids, toks, 8, 2, name="inf", head_dim=d)
+    case = setup(st, seed=10, kernel_variant=8)
+    clean, _ = _outputs(case, 8)
+    clean = clean.clone()
+    bad = 2                                # pair whose values are infinite
+    a, b = int(st.cu_seqlens[bad]), int(st.cu_seqlens[bad + 1])
+    case.online["v"][a:b] = float("inf")
+    o8, _ = _outputs(case, 8)
+    o2, _ = _outputs(case, 2)
+    keep = torch.ones(st.n_tokens, dtype=torch.bool, device=o8.device)
+    keep[a:b] = False
+    assert torch.equal(o8[keep].view(torch.int16),
+                       clean[keep].view(torch.int16))
+    assert torch.equal(torch.isnan(o8), torch.isnan(o2))
+    assert torch.equal(torch.nan_to_num(o8.float()),
+                       torch.nan_to_num(o2.float()))
