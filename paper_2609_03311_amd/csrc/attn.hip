@@ -775,25 +775,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// Pairs whose document is out of range or not resident: zero outputs and
-// -inf LSE (their token range was validated by the scheduler).  With no
-// token ranges (score mode) pair p owns row p; out may then be NULL.
+// Outputs of the pairs without a document (batches of the general scheduler).
 __global__ __launch_bounds__(256) void k_zero_invalid(
     const int32_t *counters, const int32_t *invalid, const int32_t *cu,
     int32_t Hq, int32_t D, uint16_t *out, float *lse) {
   const int32_t n_inv = counters[kCntInvalid];
-  for (int32_t idx = blockIdx.x; idx < n_inv; idx += gridDim.x) {
-    const int32_t p = invalid[idx];
-    const int64_t t0 = cu ? cu[p] : p, t1 = cu ? cu[p + 1] : p + 1;
-    const int64_t n16 = (t1 - t0) * Hq * D / 8;
-    uint4 *o = reinterpret_cast<uint4 *>(out + t0 * Hq * D);
-    if (out)
-      for (int64_t e = threadIdx.x; e < n16; e += blockDim.x)
-        o[e] = make_uint4(0, 0, 0, 0);
-    if (lse)
-      for (int64_t e = threadIdx.x; e < (t1 - t0) * Hq; e += blockDim.x)
-        lse[t0 * Hq + e] = -INFINITY;
-  }
+  for (int32_t idx = blockIdx.x; idx < n_inv; idx += gridDim.x)
+    zero_pair(invalid[idx], cu, Hq, D, out, lse);
 }
 
 // Exact mode: queue every work unit for the SAFE pass.
@@ -856,12 +844,11 @@ hipError_t launch_score_rows(const AttnParams &p, hipStream_t s) {
 // score kernel; 4 queues every unit for the exact pass instead), then the
 // exact pass over the queued units.
 template <int D>
-hipError_t launch_passes(const AttnParams &p, const KhatParams &kp,
-                         int32_t n_pairs, int shape_v, bool score,
+hipError_t launch_passes(const AttnParams &p, int shape_v, bool score,
                          hipStream_t s) {
   hipError_t e;
   switch (shape_v) {
-    case 8: e = launch_stream(D, p, kp, n_pairs, s); break;
+    case 8: e = launch_stream(D, p, s); break;
     case 7: e = launch_score_rows<D>(p, s); break;
     case 1: e = launch_variant<4, 2, false, false, D>(p, s, 0); break;
     case 3: e = launch_variant<4, 1, false, false, D>(p, s, 0); break;
@@ -930,23 +917,11 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   p.units = pl.units;
   p.qorder = pl.qorder;
   p.ntok = a->total_tokens;
-  KhatParams kp{};
-  kp.k = p.k;
-  kp.kw = p.kw;
-  kp.doc_ids = a->doc_ids;
-  kp.pair_order = pl.pair_order;
-  kp.doc_len = st.d_len;
-  kp.spair = pl.spair;
-  kp.totals = p.totals;
-  kp.rope = pl.rope;
-  kp.kh = pl.kh;
-  kp.ntok = a->total_tokens;
-  kp.Hkv = st.n_kv_heads;
-  kp.eps = a->rms_eps;
-  kp.norm = p.norm;
 
+  // (a small batch's plan has recorded the event before its k^ launch)
+  const bool small = plan_is_small(shape);
   hipError_t e;
-  if (a->timing_begin) {
+  if (a->timing_begin && !small) {
     e = hipEventRecord(static_cast<hipEvent_t>(a->timing_begin), s);
     if (e != hipSuccess) return e;
   }
@@ -977,26 +952,49 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   static_assert(small_chunks(128) * KC == kShortPrefix128,
                 "short prefixes are those two blocks per CU keep resident");
   if (score && (shape_v == 1 || shape_v == 3 || shape_v >= 8)) shape_v = 6;
-  e = D == 128 ? launch_passes<128>(p, kp, a->n_pairs, shape_v, score, s)
-               : launch_passes<64>(p, kp, a->n_pairs, shape_v, score, s);
+  if (shape_v == 8 && !small) {
+    e = launch_khat(D, khat_params(c, pl), a->n_pairs, s);
+    if (e != hipSuccess) return e;
+  }
+  e = D == 128 ? launch_passes<128>(p, shape_v, score, s)
+               : launch_passes<64>(p, shape_v, score, s);
   if (e != hipSuccess) return e;
   if (a->timing_end) {
     e = hipEventRecord(static_cast<hipEvent_t>(a->timing_end), s);
     if (e != hipSuccess) return e;
   }
-  const unsigned zgrid =
-      (unsigned)(a->n_pairs < 1024 ? (a->n_pairs > 0 ? a->n_pairs : 1) : 1024);
-  hipLaunchKernelGGL(k_zero_invalid, dim3(zgrid), dim3(256), 0, s,
-                     pl.counters, pl.invalid, score ? nullptr : a->cu_seqlens,
-                     a->n_q_heads, D, p.out, a->lse);
+  if (!small)
+    hipLaunchKernelGGL(k_zero_invalid, dim3(1024), dim3(256), 0, s,
+                       pl.counters, pl.invalid,
+                       score ? nullptr : a->cu_seqlens, a->n_q_heads, D, p.out,
+                       a->lse);
   if (score) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_score_reduce(pl, a->n_pairs, a->n_q_heads,
                                a->n_q_heads * D, c.head, s);
   }
-  (void)shape;
   return hipGetLastError();
+}
+
+KhatParams khat_params(const AttnCall &c, const Plan &pl) {
+  const dopr_attn_args_t *a = c.a;
+  const dopr_store &st = *c.st;
+  KhatParams kp{};
+  kp.k = static_cast<const uint16_t *>(a->k);
+  kp.norm = a->q_norm_w != nullptr;
+  kp.kw = kp.norm ? static_cast<const uint16_t *>(a->k_norm_w) : pl.unit_w;
+  kp.doc_ids = a->doc_ids;
+  kp.pair_order = pl.pair_order;
+  kp.doc_len = st.d_len;
+  kp.spair = pl.spair;
+  kp.totals = plan_totals(pl);
+  kp.rope = pl.rope;
+  kp.kh = pl.kh;
+  kp.ntok = a->total_tokens;
+  kp.Hkv = st.n_kv_heads;
+  kp.eps = a->rms_eps;
+  return kp;
 }
 
 }  // namespace dopr

@@ -11,9 +11,6 @@
 
 namespace dopr {
 
-int64_t *plan_totals(const Plan &pl);
-int32_t *plan_next(const Plan &pl);
-
 // Arguments of the attention kernels.
 struct AttnParams {
   const uint16_t *q, *k, *v, *qw, *kw;
@@ -66,9 +63,12 @@ struct KhatParams {
   int32_t norm;
 };
 
-// stream.hip: k_own_khat, then the streaming kernel (head size D).
-hipError_t launch_stream(int D, const AttnParams &p, const KhatParams &kp,
-                         int32_t n_pairs, hipStream_t s);
+// plan.hip: k^ of every pair's tokens (batches of the general scheduler).
+hipError_t launch_khat(int D, const KhatParams &kp, int32_t n_pairs,
+                       hipStream_t s);
+KhatParams khat_params(const AttnCall &c, const Plan &pl);
+// stream.hip: the pass kernel (head size D).
+hipError_t launch_stream(int D, const AttnParams &p, hipStream_t s);
 
 namespace {
 

@@ -29,8 +29,6 @@ constexpr int kScanThreads = 1024;
 constexpr int kScanTile = 2 * kScanThreads;
 constexpr int kThreads = 256;
 
-enum NextSlots { kNextQueues = 16 };  // 8 XCD queues + the SAFE pass
-
 inline unsigned blocks_for(int64_t n, int t) {
   int64_t b = (n + t - 1) / t;
   return (unsigned)(b < 1 ? 1 : b);
@@ -128,15 +126,6 @@ hipError_t exclusive_scan(int64_t *data, int64_t n, int64_t *blk,
                      n, blk);
   return hipGetLastError();
 }
-
-struct PlanArgs {
-  const int32_t *doc_ids, *cu, *doc_len;
-  int64_t n_docs, total_tokens;
-  int32_t n_pairs, n_rep, max_tokens, rows_per_item;
-  int32_t *status;
-  bool score_only;
-  bool exact_items;
-};
 
 __global__ __launch_bounds__(kThreads) void k_plan_init(Plan pl, int64_t n_docs,
                                                         int64_t *totals,
@@ -322,15 +311,6 @@ __global__ __launch_bounds__(kThreads) void k_items_count(Plan pl, PlanArgs a,
   pl.item_scan[g] = (rows + a.rows_per_item - 1) / a.rows_per_item;
 }
 
-// The longest-first cost class of a document group: kCostBuckets - 1 -
-// floor(log2(stacked rows * (prefix slots + 32))), clamped to the buckets
-// (0 = costliest).
-__device__ __forceinline__ uint8_t cost_class(int64_t rows, int32_t L) {
-  const int64_t cost = rows * ((int64_t)L + 32);
-  const int b = cost > 0 ? 63 - __clzll((unsigned long long)cost) : 0;
-  return (uint8_t)(kCostBuckets - 1 - (b < kCostBuckets ? b : kCostBuckets - 1));
-}
-
 // Step 5b: split a group's rows into items, boundaries on multiples of 32
 // rows: near-equal items (the block kernels, which walk an item in passes),
 // or, with exact_items, items of exactly rows_per_item rows and a shorter
@@ -357,14 +337,7 @@ __global__ __launch_bounds__(kThreads) void k_items_emit(Plan pl, PlanArgs a,
       const int64_t idx = first + it;
       if (idx >= pl.items_cap) break;
       pl.item_cls[idx] = cls;
-      const int64_t b0 =
-          a.exact_items ? base + it * a.rows_per_item
-                        : base + ((it * R / n_it) & ~(int64_t)31);
-      const int64_t b1 =
-          it + 1 < n_it
-              ? (a.exact_items ? base + (it + 1) * a.rows_per_item
-                               : base + (((it + 1) * R / n_it) & ~(int64_t)31))
-              : base + R;
+      const int64_t b0 = item_start(a, base, R, n_it, it);
       // the item's first sorted pair: the last of the group's pairs whose
       // stacked rows start at or before b0
       int32_t lo = pl.group_ptr[g], hi = pl.group_ptr[g + 1] - 1;
@@ -372,7 +345,8 @@ __global__ __launch_bounds__(kThreads) void k_items_emit(Plan pl, PlanArgs a,
         const int32_t mid = (lo + hi + 1) >> 1;
         if (pl.prow[mid] <= b0) lo = mid; else hi = mid - 1;
       }
-      pl.items[idx] = make_int4(g, (int32_t)b0, (int32_t)b1, lo);
+      pl.items[idx] = make_int4(
+          g, (int32_t)b0, (int32_t)item_start(a, base, R, n_it, it + 1), lo);
     }
   }
 }
@@ -417,90 +391,25 @@ __global__ __launch_bounds__(kThreads) void k_token_table(Plan pl, PlanArgs a,
     pl.utok[u0 + j] = make_int2(tok0 + (T - 1 - j), T - 1 - j);
 }
 
-// Bounds on the norms of every own key k^ and every query q^, each of the
-// form RoPE(RMSNorm(x) * w): an RMS-normed vector has norm <= sqrt(D), the
-// gain scales it by at most max|w|, rotation keeps it, and bf16 rounding
-// adds at most 2^-8.  bound[0] is for keys (w_k), bound[1] for queries.
-// Without QK-norm (no gains) no bound is known: both are written as 0 and
-// unit_w gets the unit gains the attention kernel multiplies by.  One
-// thread per head dim (blockDim.x = D, 64 or 128).
 __global__ __launch_bounds__(128) void k_norm_bound(const uint16_t *kw,
                                                     const uint16_t *qw,
                                                     float *bound,
                                                     uint16_t *unit_w) {
-  __shared__ float red[2][2];
-  if (!kw) unit_w[threadIdx.x] = 0x3F80;  // bf16 1.0
-  float a = 0.f, b = 0.f;
-  if (kw) a = fabsf(__uint_as_float((uint32_t)kw[threadIdx.x] << 16));
-  if (qw) b = fabsf(__uint_as_float((uint32_t)qw[threadIdx.x] << 16));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    a = fmaxf(a, __shfl_xor(a, off, 64));
-    b = fmaxf(b, __shfl_xor(b, off, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = a;
-    red[1][threadIdx.x >> 6] = b;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    const float m = blockDim.x > 64
-                        ? fmaxf(red[threadIdx.x][0], red[threadIdx.x][1])
-                        : red[threadIdx.x][0];
-    bound[threadIdx.x] = m * sqrtf((float)blockDim.x) * 1.01f;
-  }
+  __shared__ float red[4];
+  norm_bound(kw, qw, blockDim.x, red, bound, unit_w);
 }
 
-// Work units of the pass kernel, one per (item, kv head): the item's rows
-// and first pair, the document's prefix length and the element offsets of
-// its K and V^T slices for this layer and head; a unit whose logits the
-// norm bounds cannot keep within the reference-free range (the kernels'
-// kNoRefBound) is marked by its pair's sign bit and left to the exact pass.
+// Step 5e: the work units of the pass kernel, one per (item, kv head).
 __global__ __launch_bounds__(kThreads) void k_unit_table(
-    Plan pl, StoreView sv, int32_t layer, float c, float no_ref_bound,
-    int32_t n_rep, int64_t ntok, const uint16_t *v, const int64_t *totals) {
+    Plan pl, StoreView sv, UnitArgs ua, const int64_t *totals) {
   const int64_t w = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t n_items = totals[kTotItems] < pl.items_cap
                               ? totals[kTotItems]
                               : pl.items_cap;
   if (w >= n_items * sv.n_kv_heads) return;
-  const int32_t item = (int32_t)(w / sv.n_kv_heads);
-  const int32_t g = (int32_t)(w % sv.n_kv_heads);
-  const int D = sv.head_dim;
-  const int4 it = pl.items[item];
-  const int32_t doc = pl.group_doc[it.x];
-  const int32_t L = sv.doc_len[doc];
-  const int64_t blk = sv.doc_off[doc];
-  const int4 sp = pl.spair[it.w];
-  const float kb = fmaxf(
-      pl.kown[0],
-      sv.kmax[((int64_t)doc * sv.n_layers + layer) * sv.n_kv_heads + g]);
-  const bool over = c * pl.kown[1] * kb * 1.001f > no_ref_bound;
-  union {
-    PassUnit u;
-    int4 q[4];
-  } r;
-  auto put = [](int32_t *to, const uint16_t *p) {
-    to[0] = (int32_t)(uint32_t)(uint64_t)p;
-    to[1] = (int32_t)((uint64_t)p >> 32);
-  };
-  r.u.u0 = it.y / n_rep;
-  r.u.rows = (it.z - it.y) | (it.y - r.u.u0 * n_rep) << 8;
-  r.u.s = over ? it.w | INT32_MIN : it.w;
-  r.u.L = L;
-  put(r.u.k, sv.payload + k_offset(blk, L, sv.n_kv_heads, layer, g, D));
-  put(r.u.vt, sv.payload + vt_offset(blk, L, sv.n_kv_heads, layer, g, D));
-  put(r.u.own_k, pl.kh + (g * ntok + sp.x) * D);
-  put(r.u.own_v, v + ((int64_t)sp.x * sv.n_kv_heads + g) * D);
-  r.u.tok0 = sp.x;
-  r.u.T = sp.y;
-  // (positions are stacked latest first: the item's latest position of its
-  // first pair is at its first row)
-  r.u.jmax = sp.y - 1 - (it.y - sp.z) / n_rep;
-  r.u.g = g;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    reinterpret_cast<int4 *>(pl.units + w)[i] = r.q[i];
+  const int4 it = pl.items[w / sv.n_kv_heads];
+  write_unit(pl, sv, ua, w, it, pl.spair[it.w], (int32_t)(w % sv.n_kv_heads),
+             totals);
 }
 
 // Step 5f: the longest-first order of the work-unit queues.  Unit w =
@@ -585,23 +494,14 @@ __global__ __launch_bounds__(kOrderWaves * 64) void k_unit_order(
   }
 }
 
-// Step 6: rotary table, (cos, sin)(pos * omega_i) for i < half = D/2, in
-// double, stored as float; omega_i = theta^(-2i/D), or the caller's
-// inv_freq[i].
+// Step 6: the rotary table.
 __global__ __launch_bounds__(kThreads) void k_rope_table(float2 *tab,
                                                          int32_t n_pos,
                                                          int32_t half,
                                                          double log_theta,
                                                          const float *inv_freq) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= (int64_t)n_pos * half) return;
-  const int32_t pos = (int32_t)(e / half), i = (int32_t)(e % half);
-  const double freq =
-      inv_freq ? (double)inv_freq[i]
-               : exp(-(double)i / (double)half * log_theta);
-  double sn, cs;
-  sincos((double)pos * freq, &sn, &cs);
-  tab[e] = make_float2((float)cs, (float)sn);
+  rope_entry(tab, n_pos, half, log_theta, inv_freq,
+             (int64_t)blockIdx.x * kThreads + threadIdx.x);
 }
 
 }  // namespace
@@ -696,6 +596,23 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
               c.st->n_docs,      a->total_tokens,    a->n_pairs,
               c.n_rep,           a->max_tokens,      shape.rows_per_item,
               c.st->d_status,    shape.score_only, shape.stream};
+  int dev = 0, n_cu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  const int64_t lpt_units = a->queue_order == 1   ? 0
+                            : a->queue_order == 2 ? kOrderMaxUnits
+                                                  : kLptUnitsPerCu * n_cu;
+  if (plan_is_small(shape)) {
+    e = launch_plan_one(c, pl, shape, pa, lpt_units, s);
+    if (e != hipSuccess || !a->cu_seqlens) return e;
+    if (a->timing_begin) {
+      e = hipEventRecord(static_cast<hipEvent_t>(a->timing_begin), s);
+      if (e != hipSuccess) return e;
+    }
+    return launch_plan_fill(c, pl, shape, pa, s);
+  }
   int64_t *totals = plan_totals(pl);
   const int64_t P = a->n_pairs;
   const int64_t init_n = c.st->n_docs > kCounters ? c.st->n_docs : kCounters;
@@ -706,7 +623,7 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                      dim3(kThreads), 0, s, pl, pa);
   hipLaunchKernelGGL(k_doc_pack, dim3(blocks_for(c.st->n_docs, kThreads)),
                      dim3(kThreads), 0, s, pl, c.st->n_docs);
-  hipError_t e = exclusive_scan(pl.doc_scan, c.st->n_docs, pl.blk,
+  e = exclusive_scan(pl.doc_scan, c.st->n_docs, pl.blk,
                                 totals + kTotDocs, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_place, dim3(blocks_for(P, kThreads)), dim3(kThreads),
@@ -737,23 +654,13 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                      static_cast<const uint16_t *>(a->k_norm_w),
                      static_cast<const uint16_t *>(a->q_norm_w), pl.kown,
                      pl.unit_w);
-  int dev = 0, n_cu = 0;
-  e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  const int64_t lpt_units = a->queue_order == 1   ? 0
-                            : a->queue_order == 2 ? kOrderMaxUnits
-                                                  : kLptUnitsPerCu * n_cu;
   hipLaunchKernelGGL(k_unit_order, dim3(1), dim3(kOrderWaves * 64), 0, s, pl,
                      c.st->n_kv_heads, lpt_units, totals);
   if (pl.units) {
     const int64_t n_units = (int64_t)pl.items_cap * c.st->n_kv_heads;
     hipLaunchKernelGGL(k_unit_table, dim3(blocks_for(n_units, kThreads)),
-                       dim3(kThreads), 0, s, pl, c.st->view(), c.layer,
-                       a->softmax_scale * 1.4426950408889634f, kNoRefBound,
-                       c.n_rep, a->total_tokens,
-                       static_cast<const uint16_t *>(a->v), totals);
+                       dim3(kThreads), 0, s, pl, c.st->view(), unit_args(c),
+                       totals);
   }
   const double log_theta = std::log((double)a->rope_theta);
   hipLaunchKernelGGL(k_rope_table,

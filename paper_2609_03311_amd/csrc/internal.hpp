@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -167,6 +168,8 @@ struct PassUnit {
 };
 static_assert(sizeof(PassUnit) == 64, "one 16-word scalar load");
 
+enum NextSlots { kNextQueues = 16 };  // 8 XCD queues + the SAFE pass
+
 // Per-call plan built on the device by the grouping kernels (workspace).
 enum Counter {
   kCntValid = 0,     // pairs with a valid, resident document
@@ -187,7 +190,7 @@ struct Plan {
   int64_t *blk;         // scan block sums
   int32_t *pair_flag;   // [P] 1 = valid, 0 = skip, 2 = zero outputs
   int32_t *invalid;     // [P] pairs whose outputs are zeroed
-  int32_t *tmp_order;   // [P]
+  int32_t *tmp_order;   // [P] (plan.hip: the sorted pairs' groups)
   int32_t *pair_order;  // [P]
   int4 *big;            // [P / (kBigGroup + 1) + 1] groups of more than
                         // kBigGroup pairs: (first slot, pairs, doc, group)
@@ -219,6 +222,155 @@ struct Plan {
   int64_t scan_blocks_cap;
 };
 
+// Scheduler arguments of one call.
+struct PlanArgs {
+  const int32_t *doc_ids, *cu, *doc_len;
+  int64_t n_docs, total_tokens;
+  int32_t n_pairs, n_rep, max_tokens, rows_per_item;
+  int32_t *status;
+  bool score_only;
+  bool exact_items;
+};
+
+// The longest-first cost class of a document group: kCostBuckets - 1 -
+// floor(log2(stacked rows * (prefix slots + 32))), clamped to the buckets
+// (0 = costliest).
+__device__ inline uint8_t cost_class(int64_t rows, int32_t L) {
+  const int64_t cost = rows * ((int64_t)L + 32);
+  const int b = cost > 0 ? 63 - __clzll((unsigned long long)cost) : 0;
+  return (uint8_t)(kCostBuckets - 1 - (b < kCostBuckets ? b : kCostBuckets - 1));
+}
+
+// Bounds on the norms of every own key k^ and every query q^, each of the
+// form RoPE(RMSNorm(x) * w): an RMS-normed vector has norm <= sqrt(D), the
+// gain scales it by at most max|w|, rotation keeps it, and bf16 rounding
+// adds at most 2^-8.  bound[0] is for keys (w_k), bound[1] for queries.
+// Without QK-norm (no gains) no bound is known: both are written as 0 and
+// unit_w gets the unit gains the attention kernel multiplies by.  One
+// thread per head dim (64 or 128; a block's further threads only meet the
+// barrier); red: four floats of LDS.
+__device__ inline void norm_bound(const uint16_t *kw, const uint16_t *qw,
+                                  int D, float *red, float *bound,
+                                  uint16_t *unit_w) {
+  const int t = threadIdx.x;
+  float a = 0.f, b = 0.f;
+  if (t < D) {
+    if (!kw) unit_w[t] = 0x3F80;  // bf16 1.0
+    if (kw) a = fabsf(__uint_as_float((uint32_t)kw[t] << 16));
+    if (qw) b = fabsf(__uint_as_float((uint32_t)qw[t] << 16));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      a = fmaxf(a, __shfl_xor(a, off, 64));
+      b = fmaxf(b, __shfl_xor(b, off, 64));
+    }
+    if ((t & 63) == 0) {
+      red[t >> 6] = a;
+      red[2 + (t >> 6)] = b;
+    }
+  }
+  __syncthreads();
+  if (t < 2) {
+    const float m = D > 64 ? fmaxf(red[2 * t], red[2 * t + 1]) : red[2 * t];
+    bound[t] = m * sqrtf((float)D) * 1.01f;
+  }
+}
+
+// Entry e of the rotary table: (cos, sin)(pos * omega_i) for i < half = D/2,
+// in double, stored as float; omega_i = theta^(-2i/D), or the caller's
+// inv_freq[i].
+__device__ inline void rope_entry(float2 *tab, int32_t n_pos, int32_t half,
+                                  double log_theta, const float *inv_freq,
+                                  int64_t e) {
+  if (e >= (int64_t)n_pos * half) return;
+  const int32_t pos = (int32_t)(e / half), i = (int32_t)(e % half);
+  const double freq =
+      inv_freq ? (double)inv_freq[i]
+               : exp(-(double)i / (double)half * log_theta);
+  double sn, cs;
+  sincos((double)pos * freq, &sn, &cs);
+  tab[e] = make_float2((float)cs, (float)sn);
+}
+
+// First row of item `it` of a group of R rows from `base` cut into n_it items
+// (its end: the first row of item it + 1).  Boundaries lie on multiples of
+// 32 rows: near-equal items (the block kernels, which walk an item in
+// passes), or, with exact_items, items of exactly rows_per_item rows and a
+// shorter last one (the pass kernel serves an item in one pass, so no item
+// may exceed it).
+__device__ inline int64_t item_start(const PlanArgs &a, int64_t base, int64_t R,
+                                     int64_t n_it, int64_t it) {
+  if (it >= n_it) return base + R;
+  return base + (a.exact_items ? it * a.rows_per_item
+                               : (it * R / n_it) & ~(int64_t)31);
+}
+
+// What the work units' records need of the call.
+struct UnitArgs {
+  int32_t layer, n_rep;
+  float c;  // softmax_scale * log2(e)
+  int64_t ntok;
+  const uint16_t *v;
+};
+
+// Work unit w of the pass kernel: item `it`, whose first pair's record is
+// sp, for kv head g.  A unit whose logits the norm bounds cannot keep within
+// the reference-free range (kNoRefBound) is marked by its pair's sign bit
+// and left to the exact pass.
+__device__ inline void write_unit(const Plan &pl, const StoreView &sv,
+                                  const UnitArgs &ua, int64_t w,
+                                  const int4 &it, const int4 &sp, int32_t g,
+                                  const int64_t *totals) {
+  const int D = sv.head_dim;
+  const int32_t doc = pl.group_doc[it.x];
+  const int32_t L = sv.doc_len[doc];
+  const int64_t blk = sv.doc_off[doc];
+  const float kb = fmaxf(
+      pl.kown[0],
+      sv.kmax[((int64_t)doc * sv.n_layers + ua.layer) * sv.n_kv_heads + g]);
+  const bool over = ua.c * pl.kown[1] * kb * 1.001f > kNoRefBound;
+  union {
+    PassUnit u;
+    int4 q[4];
+  } r;
+  auto put = [](int32_t *to, const uint16_t *p) {
+    to[0] = (int32_t)(uint32_t)(uint64_t)p;
+    to[1] = (int32_t)((uint64_t)p >> 32);
+  };
+  r.u.u0 = it.y / ua.n_rep;
+  r.u.rows = (it.z - it.y) | (it.y - r.u.u0 * ua.n_rep) << 8;
+  r.u.s = over ? it.w | INT32_MIN : it.w;
+  r.u.L = L;
+  put(r.u.k, sv.payload + k_offset(blk, L, sv.n_kv_heads, ua.layer, g, D));
+  put(r.u.vt, sv.payload + vt_offset(blk, L, sv.n_kv_heads, ua.layer, g, D));
+  put(r.u.own_k, pl.kh + (g * ua.ntok + sp.x) * D);
+  put(r.u.own_v, ua.v + ((int64_t)sp.x * sv.n_kv_heads + g) * D);
+  r.u.tok0 = sp.x;
+  r.u.T = sp.y;
+  // (positions are stacked latest first: the item's latest position of its
+  // first pair is at its first row)
+  r.u.jmax = sp.y - 1 - (it.y - sp.z) / ua.n_rep;
+  r.u.g = g;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    reinterpret_cast<int4 *>(pl.units + w)[i] = r.q[i];
+}
+
+// Outputs of pair p, whose document is out of range or not resident: zeros
+// and -inf LSE (the scheduler validated its token range), by one block.
+// With no token ranges (score mode) pair p owns row p; out may then be NULL.
+__device__ inline void zero_pair(int32_t p, const int32_t *cu, int32_t Hq,
+                                 int32_t D, uint16_t *out, float *lse) {
+  const int64_t t0 = cu ? cu[p] : p, t1 = cu ? cu[p + 1] : p + 1;
+  const int64_t n16 = (t1 - t0) * Hq * D / 8;
+  uint4 *o = reinterpret_cast<uint4 *>(out + t0 * Hq * D);
+  if (out)
+    for (int64_t e = threadIdx.x; e < n16; e += blockDim.x)
+      o[e] = make_uint4(0, 0, 0, 0);
+  if (lse)
+    for (int64_t e = threadIdx.x; e < (t1 - t0) * Hq; e += blockDim.x)
+      lse[t0 * Hq + e] = -INFINITY;
+}
+
 // score_only: one stacked token per pair (its score token, the last one)
 // instead of all T_p.
 struct PlanShape {
@@ -233,6 +385,14 @@ struct PlanShape {
 
 size_t plan_bytes(const PlanShape &s);
 Plan plan_carve(void *ws, const PlanShape &s);
+int64_t *plan_totals(const Plan &pl);
+int32_t *plan_next(const Plan &pl);
+
+// Batches of up to this many pairs are planned by plan.hip.
+constexpr int kPlanPairs = 8192;
+inline bool plan_is_small(const PlanShape &s) {
+  return s.n_pairs <= kPlanPairs;
+}
 
 // Launchers (return hipError_t of the last launch).
 hipError_t launch_store_put(const dopr_store &st, int32_t layer, int64_t n,
@@ -252,6 +412,18 @@ struct AttnCall {
   int32_t n_rep;
   const dopr_score_head_t *head = nullptr;  // score mode (last layer)
 };
+// plan.hip: the plan of a small batch, and (with k^ where the pass kernel
+// runs, and the zero outputs of pairs without a document) its tables.
+hipError_t launch_plan_one(const AttnCall &c, const Plan &plan,
+                           const PlanShape &shape, const PlanArgs &pa,
+                           int64_t lpt_units, hipStream_t s);
+hipError_t launch_plan_fill(const AttnCall &c, const Plan &plan,
+                            const PlanShape &shape, const PlanArgs &pa,
+                            hipStream_t s);
+inline UnitArgs unit_args(const AttnCall &c) {
+  return {c.layer, c.n_rep, c.a->softmax_scale * 1.4426950408889634f,
+          c.a->total_tokens, static_cast<const uint16_t *>(c.a->v)};
+}
 hipError_t launch_plan(const AttnCall &c, const Plan &plan,
                        const PlanShape &shape, hipStream_t s);
 hipError_t launch_attention(const AttnCall &c, const Plan &plan,

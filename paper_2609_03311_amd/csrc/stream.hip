@@ -1,74 +1,12 @@
 // stream.hip -- the pass kernel of the full online layer (the automatic
-// choice unless every prefix is at most 96 slots at head size 128) and the
-// k^ precompute it reads.  Built as its own
-// translation unit with the compiler's common-code sinking off: that
+// choice unless every prefix is at most 96 slots at head size 128).  Built as
+// its own translation unit with the compiler's common-code sinking off: that
 // transformation would merge stores of different unit fields into one
 // through a pointer and move wave-uniform state to scratch memory.
 #include "attn_common.hpp"
 
 namespace dopr {
 namespace {
-
-// ---------------------------------------------------------------------------
-// k^ precompute.  One block per sorted pair: RMSNorm, gain and rotation of
-// every online key of the pair at positions L + j, for every kv head, with
-// the arithmetic of the block kernels' own-key staging (own_stage), rounded
-// to bf16 and written as k^ [Hkv][Ntok][D].  The pass kernel then copies
-// own keys like prefix keys, and a pair's keys are normed once per batch
-// instead of once per pass that reads them.
-constexpr int kKhatRowsPerStep = 2;
-
-template <int D>
-__global__ __launch_bounds__(256) void k_own_khat(KhatParams P) {
-  constexpr int NSUB = D / 16, ROWS = 256 / NSUB;
-  const int s = blockIdx.x;
-  const int n_valid = (int)(P.totals[kTotDocs] & 0xffffffff);
-  if (s >= n_valid) return;
-  const int4 sp = P.spair[s];
-  const int tok0 = sp.x, T = sp.y;
-  const int L = P.doc_len[P.doc_ids[P.pair_order[s]]];
-  const int t = threadIdx.x;
-  const int sub = t % NSUB;
-  const uint4 g0 = *reinterpret_cast<const uint4 *>(P.kw + 8 * sub);
-  const uint4 g1 = *reinterpret_cast<const uint4 *>(P.kw + D / 2 + 8 * sub);
-  const int64_t n_rows = (int64_t)T * P.Hkv;
-  // KB rows per thread and step, every row's loads issued before the first
-  // is used (the stores of one step cannot be moved above the next step's
-  // loads by the compiler, so one row per step leaves one load in flight)
-  constexpr int KB = kKhatRowsPerStep;
-  for (int64_t r0 = t / NSUB; r0 < n_rows; r0 += KB * ROWS) {
-    uint4 a0[KB], a1[KB];
-    const float4 *cq[KB];
-    int j[KB], g[KB];
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      const int64_t rr = r0 + k * ROWS < n_rows ? r0 + k * ROWS : r0;
-      j[k] = (int)(rr / P.Hkv);
-      g[k] = (int)(rr % P.Hkv);
-      const uint16_t *kr = P.k + ((int64_t)(tok0 + j[k]) * P.Hkv + g[k]) * D;
-      a0[k] = *reinterpret_cast<const uint4 *>(kr + 8 * sub);
-      a1[k] = *reinterpret_cast<const uint4 *>(kr + D / 2 + 8 * sub);
-      cq[k] = reinterpret_cast<const float4 *>(
-          P.rope + (int64_t)(L + j[k]) * (D / 2) + 8 * sub);
-    }
-    float4 c[KB][4];
-#pragma unroll
-    for (int k = 0; k < KB; ++k)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) c[k][i] = cq[k][i];
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      if (k > 0 && r0 + k * ROWS >= n_rows) break;
-      float x[16];
-      khat_part<D>(a0[k], a1[k], g0, g1, c[k][0], c[k][1], c[k][2], c[k][3],
-                   true, P.eps, P.norm != 0, x);
-      uint16_t *o = P.kh + ((int64_t)g[k] * P.ntok + tok0 + j[k]) * D;
-      *reinterpret_cast<uint4 *>(o + 8 * sub) = as_uint4(to_bf16x8(x));
-      *reinterpret_cast<uint4 *>(o + D / 2 + 8 * sub) =
-          as_uint4(to_bf16x8(x + 8));
-    }
-  }
-}
 
 __device__ __forceinline__ int rfl(int x) {
   return __builtin_amdgcn_readfirstlane(x);
@@ -698,7 +636,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
 
 }  // namespace
 
-// The pass kernel: k^ of every token first, then 4-wave blocks, two per CU
+// The pass kernel (k^ of every token is there): 4-wave blocks, two per CU
 // at head size 128 (256 registers per lane) and three at 64 (168), a
 // multiple of 8 blocks so block b serves queue b % 8.
 #ifdef DOPR_PASS_TIMERS
@@ -729,24 +667,15 @@ hipError_t launch_pass(const AttnParams &p, unsigned grid, hipStream_t s) {
 }
 }  // namespace
 
-hipError_t launch_stream(int D, const AttnParams &p, const KhatParams &kp,
-                         int32_t n_pairs, hipStream_t s) {
+hipError_t launch_stream(int D, const AttnParams &p, hipStream_t s) {
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const unsigned grid = (unsigned)((n_cu + 7) / 8 * 8);
-  if (D == 128) {
-    if (n_pairs > 0)
-      hipLaunchKernelGGL(k_own_khat<128>, dim3((unsigned)n_pairs), dim3(256),
-                         0, s, kp);
-    return launch_pass<128>(p, 2 * grid, s);
-  }
-  if (n_pairs > 0)
-    hipLaunchKernelGGL(k_own_khat<64>, dim3((unsigned)n_pairs), dim3(256), 0,
-                       s, kp);
-  return launch_pass<64>(p, 3 * grid, s);
+  return D == 128 ? launch_pass<128>(p, 2 * grid, s)
+                  : launch_pass<64>(p, 3 * grid, s);
 }
 
 }  // namespace dopr

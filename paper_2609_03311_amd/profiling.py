@@ -30,7 +30,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("csrc/attn.hip", "csrc/attn_common.hpp", "csrc/stream.hip",
-                  "csrc/internal.hpp")
+                  "csrc/plan.hip", "csrc/internal.hpp")
 # the sources each kind of summary describes (its hash is recorded with it)
 SOURCE_SETS = {
     "attention": KERNEL_SOURCES,

@@ -1,0 +1,74 @@
+"""The two-launch scheduler of small batches at the sizes where it can go
+wrong (one pair; a wave's, a block's and its own largest number of pairs; the
+first batch past it, which takes the general scheduler; document-id spaces on
+either side of the sort's digits; everything skipped), against the oracle's
+grouping, and its work items and queue orders through the attention."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_harness import compare, run, setup
+
+pytestmark = pytest.mark.gpu
+
+LIMIT = 8192  # pairs the small scheduler takes
+
+
+@pytest.mark.parametrize("n_pairs", [1, 63, 65, 1023, 1025, LIMIT - 1, LIMIT,
+                                     LIMIT + 1])
+@pytest.mark.parametrize("n_docs", [1, 255, 256, 65537])
+def test_grouping(n_pairs, n_docs):
+    import torch
+    from paper_2609_03311_amd import (dopr_check_status, dopr_group_pairs,
+                                      dopr_prefix_attn_workspace,
+                                      dopr_store_create)
+    rng = np.random.default_rng(n_pairs * 7 + n_docs)
+    lens = rng.integers(-1, 3, n_docs).astype(np.int32)
+    ids = rng.integers(-1, n_docs + 1, n_pairs)
+    hot = rng.integers(0, n_docs)
+    ids[rng.random(n_pairs) < 0.3] = hot
+    ids = ids.astype(np.int32)
+    store = dopr_store_create(1, 2, 128, lens)
+    ws = torch.empty(dopr_prefix_attn_workspace(
+        store, n_pairs=n_pairs, n_q_heads=2, max_tokens=1,
+        total_tokens=n_pairs), dtype=torch.uint8, device="cuda")
+    got = dopr_group_pairs(store, torch.from_numpy(ids).cuda(), ws)
+    for a, b in zip(got, oracle.group(ids, lens)):
+        assert np.array_equal(a.cpu().numpy(), b)
+    dopr_check_status(store)
+
+
+@pytest.mark.parametrize("variant", [8, 6])
+@pytest.mark.parametrize("order", [1, 2])
+def test_items_and_orders(variant, order):
+    """A hot document cut into many items beside short ones, and pairs
+    without a document: both queue orders, against the oracle."""
+    rng = np.random.default_rng(3 + order)
+    lens = np.array([40, 5, 300, 0, 64, -1], np.int32)
+    ids = rng.choice(6, 260, p=[.5, .1, .1, .1, .1, .1]).astype(np.int32)
+    toks = rng.choice([1, 3, 33, 70], 260).astype(np.int32)
+    st = workloads.custom(lens, ids, toks, 12, 2, name=f"items_{variant}")
+    case = setup(st, seed=21, kernel_variant=variant)
+    case.step.queue_order = order
+    assert run(case) != 0
+    bad = np.nonzero(ids == 5)[0][:4]
+    compare(case, np.sort(np.concatenate([np.arange(60), bad])))
+
+
+def test_overlapping_token_ranges_are_refused():
+    """Ranges that go back and overlap would stack more rows than the plan
+    holds: SEQLEN, and nothing is run."""
+    import torch
+    from paper_2609_03311_amd import DOPR_ERR_SEQLEN
+    st = workloads.custom(np.array([8], np.int32), np.zeros(5, np.int32),
+                          np.array([20] * 5, np.int32), 4, 2)
+    case = setup(st, seed=4, kernel_variant=8)
+    case.cu = torch.tensor([0, 100, 0, 100, 0, 100], dtype=torch.int32,
+                           device="cuda")
+    case.step.max_tokens = 100
+    case.step.workspace = torch.empty(1 << 24, dtype=torch.uint8,
+                                      device="cuda")
+    case.step.out.fill_(7.0)
+    assert run(case) == DOPR_ERR_SEQLEN
+    assert bool((case.step.out == 7.0).all())
