@@ -94,8 +94,6 @@ dopr_status_t layout_store(const dopr_store_desc_t *d, StoreLayout *lay,
   return DOPR_OK;
 }
 
-bool uses_stream_kernel(int32_t variant, const dopr_store *st);
-
 // Rows per work item: long items for the block kernels (they stage a
 // document's prefix once per item and walk the item in passes; the pass
 // kernel's items are cut to kPassRows by check_attn), and 32 for the one-wave-per-unit score kernel that the
@@ -112,14 +110,11 @@ int32_t default_rows_per_item(int32_t variant, bool score_only,
 }
 
 // The full layer runs the pass kernel for variant 8 and, in the automatic
-// choice and the self-check mode, unless every prefix is short at head size
-// 128 (at most 96 slots: two 4-wave blocks per CU keep it resident, and the
-// pass kernel's per-pass costs outweigh its savings there).  Its plan then
-// holds k^ of every token.
-bool uses_stream_kernel(int32_t variant, const dopr_store *st) {
-  if (variant == 8) return true;
-  if (variant != 0 && variant != 5) return false;
-  return !(st->head_dim == 128 && st->max_len <= kShortPrefix128);
+// choice and the self-check mode, unless the batch is small (kPassMinRows).
+// Its plan then holds k^ of every token.
+bool uses_pass_kernel(int32_t variant, int64_t rows) {
+  return variant == 8 ||
+         ((variant == 0 || variant == 5) && rows >= kPassMinRows);
 }
 
 // Validation shared by the workspace query and the attention call.
@@ -172,17 +167,22 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
       a->rows_per_item ? a->rows_per_item
                        : default_rows_per_item(a->kernel_variant, score_only,
                                                st->max_len, *n_rep);
-  shape->stream = !score_only && uses_stream_kernel(a->kernel_variant, st);
-  if (shape->stream && shape->rows_per_item > kPassRows)
-    shape->rows_per_item = kPassRows;
+  shape->stream =
+      !score_only && uses_pass_kernel(a->kernel_variant, stacked * *n_rep);
+  const int64_t rows = stacked * (int64_t)(*n_rep);
+  const auto items_of = [&](int64_t per_item) {
+    return a->n_pairs + (rows + per_item - 1) / per_item + 1;
+  };
   // work units (item, kv head) are numbered in 32 bits by the scheduler's
   // queues: the plan's item capacity times the kv heads must stay below
-  // 2^31
-  const int64_t rows = stacked * (int64_t)(*n_rep);
-  const int64_t items_cap =
-      a->n_pairs + (rows + shape->rows_per_item - 1) / shape->rows_per_item +
-      1;
-  if (items_cap * (int64_t)st->n_kv_heads > INT32_MAX)
+  // 2^31 (where only the pass kernel's short items are too many, the block
+  // kernels run)
+  if (shape->stream &&
+      items_of(kPassRows) * (int64_t)st->n_kv_heads > INT32_MAX)
+    shape->stream = false;
+  if (shape->stream && shape->rows_per_item > kPassRows)
+    shape->rows_per_item = kPassRows;
+  if (items_of(shape->rows_per_item) * (int64_t)st->n_kv_heads > INT32_MAX)
     return fail(DOPR_ERR_UNSUPPORTED,
                 "too many work units (pairs and items times kv heads must be "
                 "< 2^31)");

@@ -937,7 +937,8 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   // 7) unless some prefix is longer than kScoreRowsMaxLen (each 32-row unit
   // streams its whole prefix, so long prefixes shared by many pairs are
   // cheaper staged once per item by shape 6).  For full rows the pass kernel
-  // (shape 8) when the plan holds k^ of every token; without that buffer two
+  // (shape 8) when the plan holds k^ of every token (a batch of at least
+  // kPassMinRows stacked rows with a workspace); without that buffer two
   // 4-wave blocks per CU (half the LDS each: 96 prefix slots resident at
   // D = 128, 256 at D = 64) when every prefix fits, else one 8-wave block per
   // CU with 256 (512) slots resident.  Variants 2 and 6 keep the block-wide
@@ -949,8 +950,6 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
               : pl.kh ? 8
               : st.max_len <= small_chunks(D) * KC ? 6
                                                    : 2;
-  static_assert(small_chunks(128) * KC == kShortPrefix128,
-                "short prefixes are those two blocks per CU keep resident");
   if (score && (shape_v == 1 || shape_v == 3 || shape_v >= 8)) shape_v = 6;
   if (shape_v == 8 && !small) {
     e = launch_khat(D, khat_params(c, pl), a->n_pairs, s);

@@ -28,9 +28,15 @@ constexpr float kNoRefBound = 64.f;
 // own scratch array (one copy per device).
 constexpr size_t kNoAllocScratchBytes = DOPR_NOALLOC_SCRATCH_BYTES;
 
-// Longest prefix for which the automatic choice at head size 128 runs two
-// 4-wave blocks per CU (96 slots resident each) instead of the pass kernel.
-constexpr int32_t kShortPrefix128 = 96;
+// Stacked rows from which on the automatic choice takes the pass kernel.  In
+// a smaller batch most CUs have one work unit or none, so the call is as long
+// as its longest unit, and there the block kernels win: their prefixes are
+// resident or loaded by twice the waves, and no k^ is computed first.  Block
+// kernel -> pass kernel, us per step at head size 128: 256 to 4,096 rows 35 ->
+// 45, 40 -> 55, 46 -> 73 (prefixes of 16, 32, 250 to 500 slots); 8,192 rows
+// 55 -> 59, 65 -> 68, 76 -> 97; 16,384 rows 105 -> 94, 61 -> 63, 101 -> 75,
+// 104 -> 102; from 65,536 rows on 1071 -> 901, 1190 -> 1027, 865 -> 726.
+constexpr int64_t kPassMinRows = 16384;
 
 // Stacked rows of a work unit of the pass kernel: a 32-row tile for each of
 // a block's four waves.

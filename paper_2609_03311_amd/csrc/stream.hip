@@ -1,5 +1,5 @@
 // stream.hip -- the pass kernel of the full online layer (the automatic
-// choice unless every prefix is at most 96 slots at head size 128).  Built as
+// choice from kPassMinRows stacked rows on).  Built as
 // its own translation unit with the compiler's common-code sinking off: that
 // transformation would merge stores of different unit fields into one
 // through a pointer and move wave-uniform state to scratch memory.
