@@ -21,8 +21,12 @@
 //                 fp32 row-major [n, n] (only i <= j is written).
 // In both attention kernels the key blocks strictly below the diagonal,
 // which every row of the block sees whole, take a path without masks or
-// branches inside the head or sub-tile loops, so that one sub-tile's
-// exponentials can be scheduled against the next sub-tile's products.
+// branches inside the head or sub-tile loops, in which one tile's products
+// alternate with the exponentials of the tile before.  What bounds both is
+// the issue of a 32 x 32 tile's 8 matrix and some 60 vector instructions
+// (256 + 300 cycles, of which the chip overlaps little) at a clock that the
+// matrix power holds near 1.8 GHz, and LDS, which delivers 64 bytes a cycle
+// to a CU: each fragment read feeds two tiles.
 //   k_col_topp    per strip of 64 columns: each lane keeps the PM largest
 //                 values of its column in a sorted register list while four
 //                 waves stream interleaved rows; the lists are merged and
@@ -84,23 +88,52 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t *p) {
 // block's direct global->LDS loads overlap the products on the previous one.
 constexpr int kLdsK = kKeyBlock * D;  // bf16 elements (swizzled rows)
 
-// Keys key0 .. key0+127 of kv head g into `dst`: each lane writes 16 bytes of
-// a 1 KB block (4 key rows), fetching the global granule that the swizzled
-// layout puts in its slot, so slot p of row r holds granule p ^ swz(r).
-// Rows past the document's end repeat row n-1 (masked by the causal test).
-template <int WAVES = 4>
-__device__ __forceinline__ void stage_keys(const SalienceParams &P,
-                                           const Doc &doc, int key0, int g,
+// Rows r0 .. r0+127 of head h of the document in x [tokens, heads, D] (keys or
+// queries) into `dst`: each lane writes 16 bytes of a 1 KB block (4 rows),
+// fetching the global granule that the swizzled layout puts in its slot, so
+// slot p of row r holds granule p ^ swz(r).  Rows past the document's end
+// repeat row n-1.  Wave w takes the blocks w, w + 4, ...; a row 16 further on
+// flips bit 2 of swz.  r0 and h are wave-uniform.  The loads are written as
+// assembly so that the compiler does not know them: it would make the next
+// LDS read, of the other buffer, wait for the loads in flight.  wait_vmem and
+// the barrier behind it order them.  s_nop 4 covers the wait states after the
+// writes of the base's scalar registers and of m0, where the compiler keeps
+// nothing in these kernels.
+__device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
+                                           const Doc &doc, int r0, int h,
                                            uint16_t *dst) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst);
+  const uint16_t *base = x + ((doc.t0 + r0) * heads + h) * D;
+  const int last = doc.n - 1 - r0;
+  int row = 4 * wave + (lane >> 4);
+  // (computed here each time: kept, the eight offsets would take registers)
+  asm volatile("" : "+v"(row));
+  const uint32_t gran = ((lane & 15) ^ swz(row)) * 16;
+  const uint32_t stride = (uint32_t)(heads * D * 2);
+  if (last >= kKeyBlock - 1) {
+    const uint32_t even = (uint32_t)row * stride + gran;
+    const uint32_t odd = even ^ 64u;
 #pragma unroll
-  for (int b = wave; b < kKeyBlock / 4; b += WAVES) {
-    const int row = 4 * b + (lane >> 4), p = lane & 15;
-    const int key = min(key0 + row, doc.n - 1);
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void *)(
-            P.k + ((doc.t0 + key) * P.hkv + g) * D + ((p ^ swz(row)) << 3)),
-        (__attribute__((address_space(3))) void *)(dst + b * 512), 16, 0, 0);
+    for (int i = 0; i < kKeyBlock / 16; ++i)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                   "global_load_lds_dwordx4 %1, %2"
+                   :: "s"(lds + (wave + 4 * i) * 1024),
+                      "v"(i & 1 ? odd : even),
+                      "s"(base + (int64_t)i * 16 * heads * D)
+                   : "memory");
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < kKeyBlock / 16; ++i) {
+    const uint32_t off = (uint32_t)min(row + 16 * i, last) * stride +
+                         (gran ^ (i & 1 ? 64u : 0u));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                 "global_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds + (wave + 4 * i) * 1024), "v"(off), "s"(base)
+                 : "memory");
   }
 }
 
@@ -108,14 +141,18 @@ __device__ __forceinline__ void wait_vmem() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The A-operand fragments of key sub-tile st (keys 32 st .. 32 st + 31 of
-// the staged block, row order perm) for lane half hf.
-__device__ __forceinline__ void key_frags(const uint16_t *kbuf, int st,
-                                          int kr, int hf, bf16x8 (&kf)[8]) {
-  const int row = 32 * st + kr;
+// A lane's operand fragments of 32-row tile t of a staged block: row `r` of
+// the tile (perm(lq) for a product's key operand, lq for its q operand), lane
+// half hf.
+__device__ __forceinline__ bf16x8 row_frag(const uint16_t *buf, int t, int r,
+                                           int hf, int s) {
+  const int row = 32 * t + r;
+  return ld8(buf + row * D + (((2 * s + hf) ^ swz(row)) << 3));
+}
+__device__ __forceinline__ void row_frags(const uint16_t *buf, int t, int r,
+                                          int hf, bf16x8 (&f)[8]) {
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    kf[s] = ld8(kbuf + row * D + (((2 * s + hf) ^ swz(row)) << 3));
+  for (int s = 0; s < 8; ++s) f[s] = row_frag(buf, t, r, hf, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -180,8 +217,6 @@ __global__ __launch_bounds__(256) void k_key_norm(SalienceParams P) {
 //     exceeds 60.
 // The two lane halves are combined at the end.
 constexpr float kFixedRefMax = 60.f;
-// row blocks (of 128) from which the LSE sweep groups three per block
-constexpr int kLseGroupMinBlocks = 6;
 
 // Sum and maximum of a tile's 16 values per lane in four interleaved
 // partials, so the adds (or maxima) form chains of four, not one chain of
@@ -199,37 +234,31 @@ __device__ __forceinline__ float max16(const floatx16 &x) {
   return fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
 }
 
-// grid (row groups, kv heads, documents), longest rows first.  A block of
-// WAVES waves covers RBS = WAVES / 4 consecutive row blocks (four waves of
-// 32 rows each) and stages each key block once for all of them.  Groups
-// are aligned to the last row block, so a partial group holds the
-// shortest rows; its waves below row block 0 load clamped rows and
-// compute nothing.  Four waves: two blocks per CU in 256 registers; twelve:
-// one block per CU, three waves per SIMD in 168 registers.
-template <int HR, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(
-    WAVES == 4 ? 2 : 3, WAVES == 4 ? 2 : 3))) void k_row_lse(SalienceParams P) {
-  constexpr int RBS = WAVES / 4;
+// grid (documents x kv heads, row blocks), longest rows first: blocks that
+// follow each other, and with them the XCDs, get equally long rows (row blocks
+// as the fast dimension gave an XCD every eighth one, and with 16 of them the
+// first XCD 24 key blocks where the last had 10), and with eight kv heads an
+// XCD reads one head's keys.  16 documents of 2048 tokens, 32 q / 8 kv heads:
+// 559 -> 327 us, with one head per sweep in place of two 430; 512 documents of
+// 256 tokens, 16 / 8 heads: 253 -> 221.
+template <int HR>
+__global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
   __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
-  const int d = P.d0 + blockIdx.z;
+  const int d = P.d0 + blockIdx.x / P.hkv;
   const Doc doc = doc_at(P, d);
   if (!doc.ok) return;
-  const int nb_doc = (doc.n + kRowBlock - 1) / kRowBlock;
-  const int top = (P.max_len + kRowBlock - 1) / kRowBlock - 1 -
-                  RBS * (int)blockIdx.x;
-  if (top - RBS + 1 >= nb_doc) return;  // block-uniform, before barriers
+  const int rb = gridDim.y - 1 - blockIdx.y;
+  if (rb * kRowBlock >= doc.n) return;  // block-uniform, before barriers
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hf = lane >> 5, lq = lane & 31;
-  const int rb = top - RBS + 1 + (wave >> 2);  // this wave's row block
-  const int row0 = rb * kRowBlock + (wave & 3) * 32;
-  const bool active = rb >= 0 && row0 < doc.n;
-  const int g = blockIdx.y;
+  const int row0 = rb * kRowBlock + wave * 32;
+  const bool active = row0 < doc.n;
+  const int g = blockIdx.x % P.hkv;
   const int j = row0 + lq;
-  const int jl = min(max(j, 0), doc.n - 1);
+  const int jl = min(j, doc.n - 1);
   const int last = min(row0 + 31, doc.n - 1);
   const int64_t qrow = (doc.t0 + jl) * P.hq;
   const int kr = perm(lq);
-  const int n_kb = min(top, nb_doc - 1) + 1;  // key blocks 0 .. the last
 
   float kmax = 0.f;
 #pragma unroll
@@ -266,15 +295,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(
       for (int r = 0; r < HR; ++r) m[r] = -INFINITY;
     }
     if (h0 > 0) __syncthreads();  // the previous heads are done with ks[0]
-    stage_keys<WAVES>(P, doc, 0, g, ks[0]);
-    for (int kb = 0; kb < n_kb; ++kb) {
+    stage_rows(P.k, P.hkv, doc, 0, g, ks[0]);
+    for (int kb = 0; kb <= rb; ++kb) {
       wait_vmem();
       __syncthreads();  // block kb staged; every wave done with the other
-      if (kb + 1 < n_kb)
-        stage_keys<WAVES>(P, doc, (kb + 1) * kKeyBlock, g, ks[(kb + 1) & 1]);
-      // past this wave's diagonal, or a row block outside the document
-      // (wave-uniform; the block's barriers are all above)
-      if (RBS > 1 && (kb > rb || rb >= nb_doc)) continue;
+      if (kb < rb)
+        stage_rows(P.k, P.hkv, doc, (kb + 1) * kKeyBlock, g,
+                   ks[(kb + 1) & 1]);
       const uint16_t *kbuf = ks[kb & 1];
       const int key0 = kb * kKeyBlock;
       // below the diagonal every row sees all 128 keys: four sub-tiles in
@@ -285,34 +312,44 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(
       auto full_block = [&](auto fixed_ref) {
         constexpr bool FIXED = decltype(fixed_ref)::value;
         bf16x8 kf[8];
-        key_frags(kbuf, 0, kr, hf, kf);
+        row_frags(kbuf, 0, kr, hf, kf);
+        // unit u = (sub-tile u / HR, head u % HR); the products of unit u
+        // alternate with the exponentials of unit u - 1
+        floatx16 S[2];
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
+        for (int u = 0; u <= 4 * HR; ++u) {
+          const int st = u / HR, r = u % HR, rp = (u + HR - 1) % HR;
+          const floatx16 &T = S[(u + 1) & 1];
+          float mn = 0.f, a[4];
+          if (u > 0) mn = FIXED ? m[rp] : fmaxf(m[rp], max16(T) * P.c);
+          if (u < 4 * HR) {
 #pragma unroll
-          for (int r = 0; r < HR; ++r) {
-            floatx16 S;
+            for (int i = 0; i < 16; ++i) S[u & 1][i] = 0.f;
+          }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) S[i] = 0.f;
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-              S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[r][s], S,
-                                                          0, 0, 0);
+          for (int s = 0; s < 8; ++s) {
+            if (u < 4 * HR)
+              S[u & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  kf[s], qf[r][s], S[u & 1], 0, 0, 0);
             if (r == HR - 1 && st + 1 < 4)
-              key_frags(kbuf, st + 1, kr, hf, kf);
+              kf[s] = row_frag(kbuf, st + 1, kr, hf, s);
+            if (u > 0) {
+#pragma unroll
+              for (int i = 2 * s; i < 2 * s + 2; ++i) {
+                const float e =
+                    __builtin_amdgcn_exp2f(fmaf(T[i], P.c, -mn));
+                a[i & 3] = i < 4 ? e : a[i & 3] + e;
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (u > 0) {
+            const float sum = (a[0] + a[1]) + (a[2] + a[3]);
             if (FIXED) {
-              float e[16];
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                e[i] = __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -m[r]));
-              l[r] += sum16(e);
+              l[rp] += sum;
             } else {
-              const float mn = fmaxf(m[r], max16(S) * P.c);
-              float e[16];
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                e[i] = __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -mn));
-              l[r] = l[r] * __builtin_amdgcn_exp2f(m[r] - mn) + sum16(e);
-              m[r] = mn;
+              l[rp] = l[rp] * __builtin_amdgcn_exp2f(m[rp] - mn) + sum;
+              m[rp] = mn;
             }
           }
         }
@@ -329,11 +366,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
         if (st >= nt) break;
-        const int row = 32 * st + kr;
         bf16x8 kf[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-          kf[s] = ld8(kbuf + row * D + (((2 * s + hf) ^ swz(row)) << 3));
+        row_frags(kbuf, st, kr, hf, kf);
         // keys of this sub-tile past the wave's first row need the mask
         const bool masked = key0 + 32 * st + 31 > row0;
         const int lim = j - key0 - 32 * st - 16 * hf;  // visible: i <= lim
@@ -381,158 +415,179 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(
 
 // ---------------------------------------------------------------------------
 // Head-averaged attention.  Unit (rb, kb), kb <= rb, covers rows rb*128 ..
-// +127 and keys kb*128 .. +127, with a code path of its own for the units
-// below the diagonal (kb < rb: every row sees all 128 keys, no masks and
-// no branches in the head loop, so a sub-tile's exponentials can overlap
-// the next sub-tile's products) and for the diagonal units (kb == rb,
-// causal masks).  Each kv head's 128 key rows are staged in
-// LDS with direct global->LDS loads, double-buffered so the next kv head's
-// keys arrive while the current one is used.  Each wave walks the q heads
-// one at a time; a sub-tile's key fragments are read from LDS while the
-// previous sub-tile's exponentials run, and the next head's q fragments
-// (into the registers of the current head's, after its last product) while
-// the last sub-tile's run.
+// +127 and keys kb*128 .. +127, a 64 x 64 quarter per wave.  A wave holds its
+// keys' fragments of one kv head in registers for all of the group's q heads,
+// and reads each q fragment once for both of its 32-key tiles.  The blocks of
+// 128 rows, a kv head's keys and then each of its q heads, pass through two
+// LDS buffers: the next one's direct global->LDS loads (whole rows of 256
+// bytes) run under the current one's products.  The products of one 32 x 32
+// tile alternate with the exponentials of the tile before.  With q read from
+// memory in the operand's layout, 32 rows per wave and keys from LDS it took
+// 448 us (16 documents of 2048 tokens, 32 q / 8 kv heads) and 257 (512 of 256,
+// 16 / 8 heads), now 427 and 220; 64-key units at three waves per SIMD 612.
 template <bool DIAG>
 __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
                                                const Doc &doc, int d, int rb,
                                                int kb,
                                                uint16_t (&ks)[2][kLdsK]) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   const int hf = lane >> 5, lq = lane & 31;
-  const int row0 = rb * kRowBlock + wave * 32;
-  const bool active = row0 < doc.n;
-  const int j = row0 + lq;
-  const int jl = min(j, doc.n - 1);
-  const int key0 = kb * kKeyBlock;
-  // key sub-tiles 0 .. nt-1 hold a key some row of this wave can see
-  const int last_row = min(row0 + 31, doc.n - 1);
-  const int nt = active ? min(4, (last_row - key0) / 32 + 1) : 0;
-  const int64_t qrow = (doc.t0 + jl) * P.hq;
-  const int64_t lcol = doc.t0 + jl;
-  const int kr = perm(lq);
+  const int row0 = rb * kRowBlock, key0 = kb * kKeyBlock;
+  // the wave's row tiles rt, rt + 1 and key tiles kt, kt + 1; on the diagonal
+  // the wave above it (rt 0, kt 2) has nothing to do, and no tile is computed
+  // whose rows all come before its keys or lie past the document's end (below
+  // the diagonal those repeat the last row and are not stored, which keeps the
+  // loop free of branches)
+  const int rt = (wave >> 1) * 2, kt = (wave & 1) * 2;
+  const int end = (doc.n - 1 - row0) / 32 + 1;
 
-  floatx16 acc[4];
+  floatx16 acc[2][2];  // [row tile][key tile]
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[s][i] = 0.f;
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][k][i] = 0.f;
 
-  bf16x8 qf[8];
-  float L = 0.f, L_next = 0.f;
-  auto load_q = [&](int h) {
+  const float *lse = P.lse2 + doc.t0;
+  float L[2], Ln[2];
+  auto load_l = [&](int h) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-      qf[s] = ld8(P.q + (qrow + h) * D + 16 * s + 8 * hf);
-    L_next = P.lse2[(int64_t)h * P.total_tokens + lcol];
+    for (int t = 0; t < 2; ++t)
+      Ln[t] = lse[(int64_t)h * P.total_tokens +
+                  min(row0 + 32 * (rt + t) + lq, doc.n - 1)];
   };
-  stage_keys(P, doc, key0, 0, ks[0]);
-  // below the diagonal a wave past the document's end (rows clamped to
-  // its last row) computes anyway and stores nothing, keeping the head
-  // loop free of branches
-  if (!DIAG || active) load_q(0);
-  int g_cur = 0;
-  for (int h = 0; h < P.hq; ++h) {
-    // on a new kv head, wait for its keys (and for every wave to be done
-    // with the other buffer), then start the next kv head's keys
-    const int g = h / P.n_rep;
-    if (h == 0 || g != g_cur) {
+  int buf = 0, h = 0;
+  stage_rows(P.k, P.hkv, doc, key0, 0, ks[0]);
+  for (int g = 0; g < P.hkv; ++g) {
+    wait_vmem();
+    __syncthreads();  // the keys are staged; every wave done with the other
+    stage_rows(P.q, P.hq, doc, row0, h, ks[buf ^ 1]);
+    load_l(h);
+    bf16x8 kf[2][8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      row_frags(ks[buf], kt + k, perm(lq), hf, kf[k]);
+    for (int r = 0; r < P.n_rep; ++r, ++h) {
+      buf ^= 1;
       wait_vmem();
       __syncthreads();
-      if (g + 1 < P.hkv) stage_keys(P, doc, key0, g + 1, ks[(g + 1) & 1]);
-      g_cur = g;
-    }
-    const uint16_t *kbuf = ks[g & 1];
-    L = L_next;
-    const int hn = h + 1 < P.hq ? h + 1 : h;  // the last head reloads its own
-    if (!DIAG) {
-      bf16x8 kf[8];
-      key_frags(kbuf, 0, kr, hf, kf);
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        floatx16 S;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) S[i] = 0.f;
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-          S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], S, 0, 0,
-                                                      0);
-        if (st + 1 < 4)
-          key_frags(kbuf, st + 1, kr, hf, kf);
-        else
-          load_q(hn);
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          acc[st][i] += __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -L));
+      for (int t = 0; t < 2; ++t) L[t] = Ln[t];
+      if (r + 1 < P.n_rep) {
+        stage_rows(P.q, P.hq, doc, row0, h + 1, ks[buf ^ 1]);
+        load_l(h + 1);
+      } else if (g + 1 < P.hkv) {
+        stage_rows(P.k, P.hkv, doc, key0, g + 1, ks[buf ^ 1]);
       }
-    } else {
-      if (!active) continue;
+      const uint16_t *qbuf = ks[buf] + rt * 32 * D;
+      bf16x8 qf[8];
+      if (!DIAG) {
+        floatx16 S[2];
+        row_frags(qbuf, 0, lq, hf, qf);
+        // tile u = (row tile u / 2, key tile u % 2)
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        if (st >= nt) break;
-        bf16x8 kf[8];
-        key_frags(kbuf, st, kr, hf, kf);
-        floatx16 S;
+        for (int u = 0; u < 5; ++u) {
+          const int pt = (u + 3) / 2 - 2, pk = (u + 1) & 1;  // tile u - 1
+          if (u < 4) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) S[i] = 0.f;
+            for (int i = 0; i < 16; ++i) S[u & 1][i] = 0.f;
+          }
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-          S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], S, 0, 0,
-                                                      0);
-        const int lim = j - key0 - 32 * st - 16 * hf;  // visible: i <= lim
+          for (int s = 0; s < 8; ++s) {
+            if (u < 4)
+              S[u & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  kf[u & 1][s], qf[s], S[u & 1], 0, 0, 0);
+            if (u == 1) qf[s] = row_frag(qbuf, 1, lq, hf, s);
+            if (u > 0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          acc[st][i] += i <= lim ? __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -L))
-                                 : 0.f;
+              for (int i = 2 * s; i < 2 * s + 2; ++i)
+                acc[pt][pk][i] += __builtin_amdgcn_exp2f(
+                    fmaf(S[pk][i], P.c, -L[pt]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        continue;
       }
-      load_q(hn);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (rt + t < kt || rt + t >= end) continue;
+        row_frags(qbuf, t, lq, hf, qf);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (rt + t < kt + k) continue;
+          floatx16 S;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) S[i] = 0.f;
+#pragma unroll
+          for (int s = 0; s < 8; ++s)
+            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[k][s], qf[s], S, 0,
+                                                        0, 0);
+          // (keys after the row are computed and not stored)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            acc[t][k][i] += __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -L[t]));
+        }
+      }
     }
+    buf ^= 1;
   }
-  if (!active || j >= doc.n) return;
-  float *out = P.abar + (int64_t)(d - P.d0) * P.abar_stride +
-               (int64_t)j * P.max_len;
   const bool vec = (P.max_len & 3) == 0;  // rows 16-byte aligned
 #pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    if (st >= nt) break;
-    const int i0 = key0 + 32 * st + 16 * hf;
-    float v[16];
+  for (int t = 0; t < 2; ++t) {
+    const int j = row0 + 32 * (rt + t) + lq;
+    if (j >= doc.n) continue;
+    float *out = P.abar + (int64_t)(d - P.d0) * P.abar_stride +
+                 (int64_t)j * P.max_len;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = acc[st][i] * P.inv_hq;
-    if (vec && i0 + 16 <= j + 1) {
+    for (int k = 0; k < 2; ++k) {
+      const int i0 = key0 + 32 * (kt + k) + 16 * hf;
+      float v[16];
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        *reinterpret_cast<float4 *>(out + i0 + 4 * c) =
-            make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
-    } else {
+      for (int i = 0; i < 16; ++i) v[i] = acc[t][k][i] * P.inv_hq;
+      if (vec && i0 + 16 <= j + 1) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (i0 + i <= j) out[i0 + i] = v[i];
+        for (int c = 0; c < 4; ++c)
+          *reinterpret_cast<float4 *>(out + i0 + 4 * c) =
+              make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (i0 + i <= j) out[i0 + i] = v[i];
+      }
     }
   }
 }
 
-// grid (units, docs): the nb diagonal units first (their waves see 1 to 4
-// sub-tiles, so they are kept out of the launch's tail), then the units
-// below the diagonal, unit nb + t with t = rb (rb - 1) / 2 + kb.
+// grid: the units of each document one after another, unit rb (rb + 1) / 2 +
+// kb, in runs of kUnitRun that go to the XCDs in turn (block b runs on XCD
+// b % 8): units that follow each other share their rows' q through one L2.
+constexpr int kUnitRun = 32;
 __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
-                                                      int32_t nb) {
+                                                      int32_t nb,
+                                                      int32_t n_docs) {
   __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
-  const int d = P.d0 + blockIdx.y;
+  const int slot = blockIdx.x / 8;
+  const int unit =
+      (slot / kUnitRun * 8 + blockIdx.x % 8) * kUnitRun + slot % kUnitRun;
+  const int per = nb * (nb + 1) / 2;
+  const int dd = unit / per, t = unit % per;
+  if (dd >= n_docs) return;  // block-uniform, before any barrier
+  const int d = P.d0 + dd;
   const Doc doc = doc_at(P, d);
   if (!doc.ok) return;
-  if ((int)blockIdx.x < nb) {  // block-uniform
-    const int rb = blockIdx.x;
-    if (rb * kRowBlock >= doc.n) return;  // before any barrier
-    mean_attn_unit<true>(P, doc, d, rb, rb, ks);
-  } else {
-    const int t = blockIdx.x - nb;
-    int rb = (int)((sqrtf(8.f * t + 1.f) + 1.f) * 0.5f);
-    while (rb * (rb - 1) / 2 > t) --rb;
-    while ((rb + 1) * rb / 2 <= t) ++rb;
-    const int kb = t - rb * (rb - 1) / 2;
-    if (rb * kRowBlock >= doc.n) return;  // before any barrier
+  int rb = __builtin_amdgcn_readfirstlane(
+      (int)((sqrtf(8.f * t + 1.f) - 1.f) * 0.5f));
+  while (rb * (rb + 1) / 2 > t) --rb;
+  while ((rb + 1) * (rb + 2) / 2 <= t) ++rb;
+  const int kb = t - rb * (rb + 1) / 2;
+  if (rb * kRowBlock >= doc.n) return;  // before any barrier
+  if (kb < rb)  // block-uniform
     mean_attn_unit<false>(P, doc, d, rb, kb, ks);
-  }
+  else
+    mean_attn_unit<true>(P, doc, d, rb, kb, ks);
 }
 
 // ---------------------------------------------------------------------------
@@ -703,21 +758,17 @@ hipError_t launch_salience_chunk(const SalienceParams &p, int32_t n_docs,
                                  int hr, int pm, hipStream_t s) {
   if (n_docs == 0) return hipSuccess;
   const int nb = (p.max_len + kRowBlock - 1) / kRowBlock;
-  const dim3 g_lse(nb, p.hkv, n_docs);
-  const dim3 g_att(nb * (nb + 1) / 2, n_docs);
+  const dim3 g_lse(n_docs * p.hkv, nb);
+  const int64_t units = (int64_t)nb * (nb + 1) / 2 * n_docs;
+  constexpr int kRun8 = 8 * kUnitRun;
+  const dim3 g_att((unsigned)((units + kRun8 - 1) / kRun8 * kRun8));
   const dim3 g_col((p.max_len + kStrip - 1) / kStrip, n_docs);
-  // long documents: three row blocks per block at three waves per SIMD
-  // (one q head per sweep); short ones keep enough blocks with one row
-  // block each
-  if (nb >= kLseGroupMinBlocks) {
-    hipLaunchKernelGGL((k_row_lse<1, 12>), dim3((nb + 2) / 3, p.hkv, n_docs),
-                       dim3(768), 0, s, p);
-  } else if (hr == 2) {
-    hipLaunchKernelGGL((k_row_lse<2, 4>), g_lse, dim3(256), 0, s, p);
-  } else {
-    hipLaunchKernelGGL((k_row_lse<1, 4>), g_lse, dim3(256), 0, s, p);
-  }
-  hipLaunchKernelGGL(k_mean_attn, g_att, dim3(256), 0, s, p, (int32_t)nb);
+  if (hr == 2)
+    hipLaunchKernelGGL(k_row_lse<2>, g_lse, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL(k_row_lse<1>, g_lse, dim3(256), 0, s, p);
+  hipLaunchKernelGGL(k_mean_attn, g_att, dim3(256), 0, s, p, (int32_t)nb,
+                     n_docs);
   if (pm == 8)
     hipLaunchKernelGGL(k_col_topp<8>, g_col, dim3(256), 0, s, p);
   else if (pm == 16)
