@@ -474,7 +474,7 @@ int launch_layer_post(const LayerShape &s, const dopr_layer_args_t *l,
 const char *gemm_status_str(int s);
 
 // Offline salience selection (salience.hip).
-constexpr int kSalienceMaxLen = 4096;   // longest document (LDS sort bound)
+constexpr int kSalienceMaxLen = 4096;   // longest document (keys in LDS)
 constexpr int kSalienceMaxP = 64;       // largest top-p (register list bound)
 constexpr size_t kSalienceAbarBudget = size_t(1) << 30;  // scratch bytes
 

@@ -31,8 +31,8 @@
 //                 values of its column in a sorted register list while four
 //                 waves stream interleaved rows; the lists are merged and
 //                 the top m averaged.
-//   k_topk        per document: bitonic sort of (u, position) keys in LDS,
-//                 then an ordered compaction of the chosen positions.
+//   k_topk        per document: radix search of the K-th largest u, then an
+//                 ordered compaction of the chosen positions.
 //
 // Both attention kernels form S = K Q^T with the 32x32x16 bf16 MFMA in the
 // same operand layout and the same k order, so the logits they see are the
@@ -54,6 +54,11 @@ constexpr int D = kHeadDim;
 constexpr int kRowBlock = 128;   // rows per unit (4 waves x 32)
 constexpr int kKeyBlock = 128;   // keys per mean-attention unit
 constexpr int kStrip = 64;       // columns per top-p strip
+// Longest document from which a strip's columns are split over more than four
+// waves: from there the chain of loads outweighs the longer merge (one
+// document of 512 tokens, whole call: 105 -> 102 us, of 1024 135 -> 125, of
+// 2048 189 -> 166; 512 of 256 tokens, this kernel alone: 41 -> 62).
+constexpr int kToppWideLen = 512;
 
 __device__ __forceinline__ int perm(int m) {
   return ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3);
@@ -591,10 +596,13 @@ __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
 }
 
 // ---------------------------------------------------------------------------
-// Column top-p means.  grid (strips of 64 columns, docs); the 4 waves of a
-// block stream rows j = c0 + w, c0 + w + 4, ... of the strip; lane l keeps
+// Column top-p means.  grid (strips of 64 columns, docs); the W waves of a
+// block stream rows j = c0 + w, c0 + w + W, ... of the strip; lane l keeps
 // the PM largest values of column c0 + l (descending, -1 = empty) and the
-// lists are merged through LDS at the end.
+// lists are merged through LDS at the end, half of them into the other half
+// at a time.  A wave walks its rows eight loads at a time, so the longest
+// column is a chain of n / 8W memory latencies: 16 documents of 2048 tokens
+// take 48 us with 16 waves and 67 with four.
 template <int PM>
 __device__ __forceinline__ void insert(float (&L)[PM], float v) {
 #pragma unroll
@@ -605,14 +613,14 @@ __device__ __forceinline__ void insert(float (&L)[PM], float v) {
   }
 }
 
-template <int PM>
-__global__ __launch_bounds__(256) void k_col_topp(SalienceParams P) {
-  __shared__ float merge[3][PM][kStrip];
+template <int PM, int W>
+__global__ __launch_bounds__(64 * W) void k_col_topp(SalienceParams P) {
+  __shared__ float merge[W / 2][PM][kStrip];
   const int d = P.d0 + blockIdx.y;
   const Doc doc = doc_at(P, d);
   if (!doc.ok) return;
   const int c0 = blockIdx.x * kStrip;
-  if (c0 >= doc.n) return;  // block-uniform, before the barrier
+  if (c0 >= doc.n) return;  // block-uniform, before the barriers
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int c = c0 + lane;
   const bool col = c < doc.n;
@@ -623,33 +631,37 @@ __global__ __launch_bounds__(256) void k_col_topp(SalienceParams P) {
   for (int k = 0; k < PM; ++k) L[k] = -1.f;
   constexpr int U = 8;
   int j = c0 + wave;
-  for (; j + 4 * (U - 1) < doc.n; j += 4 * U) {
+  for (; j + W * (U - 1) < doc.n; j += W * U) {
     float v[U];
 #pragma unroll
     for (int x = 0; x < U; ++x)
-      v[x] = base[(int64_t)(j + 4 * x) * P.max_len];
+      v[x] = base[(int64_t)(j + W * x) * P.max_len];
 #pragma unroll
     for (int x = 0; x < U; ++x) {
-      const float w = (col && j + 4 * x >= c) ? v[x] : -1.f;
+      const float w = (col && j + W * x >= c) ? v[x] : -1.f;
       if (__any(w > L[PM - 1])) insert(L, w);
     }
   }
-  for (; j < doc.n; j += 4) {
+  for (; j < doc.n; j += W) {
     const float v = base[(int64_t)j * P.max_len];
     const float w = (col && j >= c) ? v : -1.f;
     if (__any(w > L[PM - 1])) insert(L, w);
   }
-  if (wave > 0) {
+  for (int half = W / 2; half > 0; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
 #pragma unroll
-    for (int k = 0; k < PM; ++k) merge[wave - 1][k][lane] = L[k];
-  }
-  __syncthreads();
-  if (wave != 0 || !col) return;
-  for (int w = 0; w < 3; ++w)
-    for (int k = 0; k < PM; ++k) {
-      const float v = merge[w][k][lane];
-      if (__any(v > L[PM - 1])) insert(L, v);
+      for (int k = 0; k < PM; ++k) merge[wave - half][k][lane] = L[k];
     }
+    __syncthreads();
+    if (wave < half) {
+      for (int k = 0; k < PM; ++k) {
+        const float v = merge[wave][k][lane];
+        if (__any(v > L[PM - 1])) insert(L, v);
+      }
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || !col) return;
   const int m = min(P.top_p, doc.n - c);
   float sum = 0.f;
 #pragma unroll
@@ -671,9 +683,13 @@ __global__ __launch_bounds__(256) void k_check(SalienceParams P) {
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Top-K selection.  One block per document; keys (orderable u bits << 32 |
-// ~position) sorted descending by a bitonic network in LDS, the first K
-// positions flagged and compacted in position order.
+// Top-K selection.  One block per document: the K-th largest key (the
+// orderable bits of u) is found eight bits at a time from a histogram of the
+// keys that share the bits found so far; the keys above it, and of those equal
+// to it as many as are missing, the lowest positions first, are written in
+// position order.  Four short passes, bound by their barriers, where a bitonic
+// sort of the keys took 66 to 78 (documents of 2048 tokens 34 -> 10 us, 512 of
+// 256 tokens 17 -> 10).
 namespace {
 
 constexpr int kTopkThreads = 1024;
@@ -684,8 +700,9 @@ __device__ __forceinline__ uint32_t orderable(float f) {
 }
 
 __global__ __launch_bounds__(kTopkThreads) void k_topk(TopkParams P) {
-  __shared__ uint64_t key[kSalienceMaxLen];
-  __shared__ uint8_t flag[kSalienceMaxLen];
+  __shared__ uint32_t key[kSalienceMaxLen];
+  __shared__ int32_t hist[256];
+  __shared__ int32_t found[2];  // the bin of the K-th key, keys above it
   __shared__ int32_t wsum[kTopkThreads / 64];
   const int d = blockIdx.x;
   const int32_t a = P.cu[d], b = P.cu[d + 1];
@@ -706,38 +723,49 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(TopkParams P) {
     for (int i = threadIdx.x; i < n; i += kTopkThreads) out[i] = i;
     return;
   }
-  int N2 = 1;
-  while (N2 < n) N2 <<= 1;
-  const float *u = P.u + a;
-  for (int i = threadIdx.x; i < N2; i += kTopkThreads)
-    key[i] = i < n ? ((uint64_t)orderable(u[i]) << 32) | (uint32_t)~i : 0ull;
-  __syncthreads();
-  for (int k = 2; k <= N2; k <<= 1)
-    for (int s = k >> 1; s > 0; s >>= 1) {
-      for (int i = threadIdx.x; i < N2; i += kTopkThreads) {
-        const int x = i ^ s;
-        if (x > i) {
-          const uint64_t p = key[i], q = key[x];
-          const bool desc = (i & k) == 0;
-          if (desc ? p < q : p > q) {
-            key[i] = q;
-            key[x] = p;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int i = threadIdx.x; i < n; i += kTopkThreads) flag[i] = 0;
-  __syncthreads();
-  for (int r = threadIdx.x; r < K; r += kTopkThreads)
-    flag[~(uint32_t)key[r]] = 1;
-  __syncthreads();
-  // ordered compaction: thread t owns positions [t*per, (t+1)*per)
-  const int per = (n + kTopkThreads - 1) / kTopkThreads;
-  const int p0 = threadIdx.x * per;
-  int cnt = 0;
-  for (int i = p0; i < min(p0 + per, n); ++i) cnt += flag[i];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float *u = P.u + a;
+  for (int i = threadIdx.x; i < n; i += kTopkThreads) key[i] = orderable(u[i]);
+  uint32_t kth = 0;  // the K-th largest key's bits above `shift`
+  int need = K;      // keys still to take among those that share them
+  for (int shift = 24; shift >= 0; shift -= 8) {
+    const uint32_t seen = shift == 24 ? 0u : ~0u << (shift + 8);
+    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kTopkThreads)
+      if (((key[i] ^ kth) & seen) == 0)
+        atomicAdd(&hist[(key[i] >> shift) & 255], 1);
+    __syncthreads();
+    if (wave == 0) {
+      // lane l: bins 255 - 4l down to 252 - 4l
+      int c[4], own = 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) own += c[x] = hist[255 - 4 * lane - x];
+      int incl = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      int above = incl - own;
+      if (above < need && need <= incl) {  // one lane
+        int x = 0;
+        while (above + c[x] < need) above += c[x++];
+        found[0] = 255 - 4 * lane - x;
+        found[1] = above;
+      }
+    }
+    __syncthreads();
+    kth |= (uint32_t)found[0] << shift;
+    need -= found[1];
+  }
+  // ordered compaction: thread t owns positions [t*per, (t+1)*per); counts of
+  // keys above the K-th in the low half, of equal ones in the high half
+  const int per = (n + kTopkThreads - 1) / kTopkThreads;
+  const int p0 = threadIdx.x * per, p1 = min(p0 + per, n);
+  int cnt = 0;
+  for (int i = p0; i < p1; ++i)
+    cnt += key[i] > kth ? 1 : key[i] == kth ? 1 << 16 : 0;
   int incl = cnt;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -748,8 +776,22 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(TopkParams P) {
   __syncthreads();
   int before = incl - cnt;
   for (int w = 0; w < wave; ++w) before += wsum[w];
-  for (int i = p0; i < min(p0 + per, n); ++i)
-    if (flag[i]) out[before++] = i;
+  int gt = before & 0xffff, eq = before >> 16;
+  for (int i = p0; i < p1; ++i) {
+    const bool more = key[i] > kth, same = key[i] == kth;
+    if (more || (same && eq < need)) out[gt + min(eq, need)] = i;
+    gt += more;
+    eq += same;
+  }
+}
+
+template <int PM>
+void launch_col_topp(const SalienceParams &p, dim3 grid, hipStream_t s) {
+  constexpr int W = PM <= 16 ? 16 : PM <= 32 ? 8 : 4;
+  if (W > 4 && p.max_len >= kToppWideLen)
+    hipLaunchKernelGGL((k_col_topp<PM, W>), grid, dim3(64 * W), 0, s, p);
+  else
+    hipLaunchKernelGGL((k_col_topp<PM, 4>), grid, dim3(256), 0, s, p);
 }
 
 }  // namespace
@@ -770,13 +812,13 @@ hipError_t launch_salience_chunk(const SalienceParams &p, int32_t n_docs,
   hipLaunchKernelGGL(k_mean_attn, g_att, dim3(256), 0, s, p, (int32_t)nb,
                      n_docs);
   if (pm == 8)
-    hipLaunchKernelGGL(k_col_topp<8>, g_col, dim3(256), 0, s, p);
+    launch_col_topp<8>(p, g_col, s);
   else if (pm == 16)
-    hipLaunchKernelGGL(k_col_topp<16>, g_col, dim3(256), 0, s, p);
+    launch_col_topp<16>(p, g_col, s);
   else if (pm == 32)
-    hipLaunchKernelGGL(k_col_topp<32>, g_col, dim3(256), 0, s, p);
+    launch_col_topp<32>(p, g_col, s);
   else
-    hipLaunchKernelGGL(k_col_topp<64>, g_col, dim3(256), 0, s, p);
+    launch_col_topp<64>(p, g_col, s);
   return hipGetLastError();
 }
 

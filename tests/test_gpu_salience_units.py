@@ -5,7 +5,8 @@ Tolerances as derived in test_gpu_salience."""
 import numpy as np
 import pytest
 
-from test_gpu_salience import _free, check_doc, oracle_for, run_case
+from test_gpu_salience import (_free, check_doc, cpu_top_k, oracle_for,
+                               run_case)
 
 pytestmark = pytest.mark.gpu
 
@@ -23,3 +24,44 @@ def test_units_of_ragged_batches(hq, hkv, p):
         check_doc(step, d, ora)
     del step
     _free()
+
+
+@pytest.mark.parametrize("n,p", [(511, 8), (512, 8), (513, 16), (640, 32),
+                                 (515, 64)])
+def test_wide_strips_and_selection(n, p):
+    """Both sides of the length from which a strip has more waves, every list
+    size."""
+    lens = [n, 3, n - 130]
+    step, q, k = run_case(lens, 4, 2, p, n_select=[n // 3, 1, n - 131],
+                          seed=30 + p, with_attention=False)
+    ora = oracle_for(step, q, k, p, range(3), with_attention=False)
+    for d in range(3):
+        check_doc(step, d, ora, with_attention=False)
+    del step
+    _free()
+
+
+def test_selection_of_equal_values():
+    """All u equal, two values, infinities and zeros of both signs: the lower
+    positions are taken first."""
+    import torch
+    import paper_2609_03311_amd as D
+    n = 1000
+    rng = np.random.default_rng(5)
+    rows = [np.zeros(n), np.full(n, 0.25), rng.choice([0.5, 0.25], n),
+            rng.choice([np.inf, 1e-30, 0.0, 3.0], n),
+            np.float32(1) + rng.integers(0, 40, n) * 2.0 ** -23]
+    u = torch.tensor(np.concatenate(rows), dtype=torch.float32,
+                     device="cuda")
+    cu = torch.arange(0, (len(rows) + 1) * n, n, dtype=torch.int32,
+                      device="cuda")
+    for k in (1, 333, 999):
+        cs = torch.arange(0, (len(rows) + 1) * k, k, dtype=torch.int32,
+                          device="cuda")
+        sel = torch.full((len(rows) * k,), -1, dtype=torch.int32,
+                         device="cuda")
+        D.dopr_select_top_k(cu, cs, u, sel, max_doclen=n)
+        torch.cuda.synchronize()
+        for r, x in enumerate(rows):
+            got = sel[r * k:(r + 1) * k].cpu().numpy()
+            assert np.array_equal(got, cpu_top_k(x.astype(np.float32), k))
