@@ -239,7 +239,7 @@ __device__ __forceinline__ float max16(const floatx16 &x) {
   return fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
 }
 
-// grid (documents x kv heads, row blocks), longest rows first: blocks that
+// grid (kv heads, documents, row blocks), longest rows first: blocks that
 // follow each other, and with them the XCDs, get equally long rows (row blocks
 // as the fast dimension gave an XCD every eighth one, and with 16 of them the
 // first XCD 24 key blocks where the last had 10), and with eight kv heads an
@@ -249,16 +249,16 @@ __device__ __forceinline__ float max16(const floatx16 &x) {
 template <int HR>
 __global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
   __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
-  const int d = P.d0 + blockIdx.x / P.hkv;
+  const int d = P.d0 + blockIdx.y;
   const Doc doc = doc_at(P, d);
   if (!doc.ok) return;
-  const int rb = gridDim.y - 1 - blockIdx.y;
+  const int rb = gridDim.z - 1 - blockIdx.z;
   if (rb * kRowBlock >= doc.n) return;  // block-uniform, before barriers
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hf = lane >> 5, lq = lane & 31;
   const int row0 = rb * kRowBlock + wave * 32;
   const bool active = row0 < doc.n;
-  const int g = blockIdx.x % P.hkv;
+  const int g = blockIdx.x;
   const int j = row0 + lq;
   const int jl = min(j, doc.n - 1);
   const int last = min(row0 + 31, doc.n - 1);
@@ -800,7 +800,7 @@ hipError_t launch_salience_chunk(const SalienceParams &p, int32_t n_docs,
                                  int hr, int pm, hipStream_t s) {
   if (n_docs == 0) return hipSuccess;
   const int nb = (p.max_len + kRowBlock - 1) / kRowBlock;
-  const dim3 g_lse(n_docs * p.hkv, nb);
+  const dim3 g_lse(p.hkv, n_docs, nb);
   const int64_t units = (int64_t)nb * (nb + 1) / 2 * n_docs;
   constexpr int kRun8 = 8 * kUnitRun;
   const dim3 g_att((unsigned)((units + kRun8 - 1) / kRun8 * kRun8));
