@@ -24,9 +24,8 @@
 // branches inside the head or sub-tile loops, in which one tile's products
 // alternate with the exponentials of the tile before.  What bounds both is
 // the issue of a 32 x 32 tile's 8 matrix and some 60 vector instructions
-// (256 + 300 cycles, of which the chip overlaps little) at a clock that the
-// matrix power holds near 1.8 GHz, and LDS, which delivers 64 bytes a cycle
-// to a CU: each fragment read feeds two tiles.
+// (256 + 300 cycles, of which the chip overlaps a part) at a clock that the
+// matrix power holds near 1.8 GHz; each fragment read feeds two tiles.
 //   k_col_topp    per strip of 64 columns: each lane keeps the PM largest
 //                 values of its column in a sorted register list while four
 //                 waves stream interleaved rows; the lists are merged and
