@@ -117,6 +117,20 @@ bool uses_pass_kernel(int32_t variant, int64_t rows) {
          ((variant == 0 || variant == 5) && rows >= kPassMinRows);
 }
 
+// Shapes that the pass kernel's 32-bit arithmetic holds; the block kernels
+// serve the others, with the same bits.  It keeps a unit's first head in the
+// upper 24 bits of a word and divides a row by n_rep with a multiplied
+// reciprocal, exact while (128 + n_rep) * n_rep < 2^32 (from n_rep = 65,537 on
+// it is not: row 65,536 of the first token would count as the second's), and it
+// takes byte offsets of a chunk's V^T rows (up to D rows of the prefix) and of
+// a chunk's own v rows (64 tokens) in 32 bits.
+bool pass_kernel_holds(const dopr_store *st, int32_t n_rep) {
+  const int64_t D = st->head_dim;
+  return n_rep < (1 << 15) &&
+         2 * D * (int64_t)pad8(st->max_len) <= UINT32_MAX &&
+         st->n_kv_heads * D < (1 << 25);
+}
+
 // Validation shared by the workspace query and the attention call.
 dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
                          PlanShape *shape, int32_t *n_rep,
@@ -168,7 +182,8 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
                        : default_rows_per_item(a->kernel_variant, score_only,
                                                st->max_len, *n_rep);
   shape->stream =
-      !score_only && uses_pass_kernel(a->kernel_variant, stacked * *n_rep);
+      !score_only && uses_pass_kernel(a->kernel_variant, stacked * *n_rep) &&
+      pass_kernel_holds(st, *n_rep);
   const int64_t rows = stacked * (int64_t)(*n_rep);
   const auto items_of = [&](int64_t per_item) {
     return a->n_pairs + (rows + per_item - 1) / per_item + 1;
@@ -395,7 +410,6 @@ dopr_status_t noalloc_too_large(size_t need) {
 // 128-row items is beyond it runs the block kernels, which give the same
 // bits.
 dopr_status_t noalloc_shape(const dopr_attn_args_t *a, PlanShape *shape) {
-  if (!shape->stream) return DOPR_OK;
   PlanShape block = *shape;
   block.stream = false;
   block.rows_per_item = a->rows_per_item ? a->rows_per_item : 2048;
@@ -409,7 +423,8 @@ dopr_status_t noalloc_shape(const dopr_attn_args_t *a, PlanShape *shape) {
                      shape->head_dim, kAlign) +
         align_up(32 * (size_t)cap * shape->n_kv_heads, kAlign);
     if (need > kNoAllocScratchBytes) return noalloc_too_large(need);
-    if (plan_bytes(*shape) <= kNoAllocScratchBytes) return DOPR_OK;
+    if (shape->stream && plan_bytes(*shape) <= kNoAllocScratchBytes)
+      return DOPR_OK;
   }
   *shape = block;
   return DOPR_OK;

@@ -497,7 +497,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   const uint32_t ring =
       lds_addr(sm.batch[0]) + wave * (KC * D * 2 / 1024 / 4) * 1024;
   const int n_rep = P0.n_rep, stride = P0.Hkv * D;
-  // (x / n_rep = umulhi(x, rep_mul) for x < 128 + n_rep; n_rep < 2^15)
+  // (x / n_rep = umulhi(x, rep_mul) for x < 128 + n_rep: the host admits n_rep
+  // < 2^15)
   const uint32_t rep_mul = n_rep > 1 ? 0xffffffffu / (uint32_t)n_rep + 1 : 0;
   const FeedLane fl = feed_lane<D>(wave, lane, stride);
 

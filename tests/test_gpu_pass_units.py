@@ -108,3 +108,28 @@ def test_automatic_choice_on_both_sides_of_its_line(slots, tokens):
             for v in (0, 2)]
     khat = 2 * tokens * 2 * 128
     assert (need[0] >= need[1] + khat) == (tokens == 4096)
+
+
+@pytest.mark.parametrize("n_rep", [(1 << 15) - 1, 1 << 15, 65537])
+def test_groups_of_many_heads(n_rep):
+    """The pass kernel divides rows by n_rep with a multiplied reciprocal and
+    keeps a head number in 24 bits: from 2^15 heads per kv head on the block
+    kernels run in its place (at 65,537 the reciprocal would take a row of one
+    token for the next token's)."""
+    import torch
+    import paper_2609_03311_amd as D
+    toks = np.array([2, 1, 2], np.int32)
+    st = workloads.custom(np.array([5, 33], np.int32),
+                          np.array([0, 1, 0], np.int32), toks, n_rep, 1,
+                          name=f"heads_{n_rep}", head_dim=64)
+    case = setup(st, seed=12, kernel_variant=2)
+    need = {v: D.dopr_prefix_attn_workspace(
+                case.store, n_pairs=3, n_q_heads=n_rep, max_tokens=2,
+                total_tokens=5, kernel_variant=v) for v in (0, 8, 2)}
+    for v in (0, 8):
+        assert (need[v] > need[2]) == (n_rep < 1 << 15), (v, need)
+    out2, lse2 = _outputs(case, 2)
+    for v in (8, 0):
+        out, lse = _outputs(case, v)
+        assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+        assert torch.equal(lse, lse2)
