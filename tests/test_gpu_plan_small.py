@@ -56,6 +56,18 @@ def test_items_and_orders(variant, order):
     compare(case, np.sort(np.concatenate([np.arange(60), bad])))
 
 
+def _attend(case):
+    """The attention alone (the score head reads the row of each pair's last
+    token, which malformed ranges put outside the batch)."""
+    import torch
+    from paper_2609_03311_amd import dopr_check_status
+    o, p = case.online, case.prm
+    case.step.attention(0, case.doc_ids, case.cu, o["q"], o["k"], o["v"],
+                        p["q_norm_w"], p["k_norm_w"])
+    torch.cuda.synchronize()
+    return dopr_check_status(case.store)
+
+
 def test_overlapping_token_ranges_are_refused():
     """Ranges that go back and overlap would stack more rows than the plan
     holds: SEQLEN, and nothing is run."""
@@ -70,5 +82,5 @@ def test_overlapping_token_ranges_are_refused():
     case.step.workspace = torch.empty(1 << 24, dtype=torch.uint8,
                                       device="cuda")
     case.step.out.fill_(7.0)
-    assert run(case) == DOPR_ERR_SEQLEN
+    assert _attend(case) == DOPR_ERR_SEQLEN
     assert bool((case.step.out == 7.0).all())
