@@ -991,6 +991,7 @@ KhatParams khat_params(const AttnCall &c, const Plan &pl) {
   kp.rope = pl.rope;
   kp.kh = pl.kh;
   kp.ntok = a->total_tokens;
+  kp.rows_cap = a->total_tokens * c.n_rep;  // (full rows only)
   kp.Hkv = st.n_kv_heads;
   kp.eps = a->rms_eps;
   return kp;

@@ -57,7 +57,7 @@ struct KhatParams {
   const int64_t *totals;
   const float2 *rope;
   uint16_t *kh;
-  int64_t ntok;
+  int64_t ntok, rows_cap;
   int32_t Hkv;
   float eps;
   int32_t norm;

@@ -297,11 +297,13 @@ __global__ __launch_bounds__(1024) void k_rank_big(Plan pl, PlanArgs a) {
   }
 }
 
-// Step 5a: work items per group.
+// Step 5a: work items per group.  From here on the stacked rows are known:
+// plan_groups and plan_pairs give none when they exceed the tables, so nothing
+// is written and nothing runs.
 __global__ __launch_bounds__(kThreads) void k_items_count(Plan pl, PlanArgs a,
                                                           const int64_t *totals) {
   const int32_t g = blockIdx.x * kThreads + threadIdx.x;
-  const int32_t n_groups = (int32_t)(totals[kTotDocs] >> 32);
+  const int32_t n_groups = plan_groups(totals, a.rows_cap);
   if (g > a.n_pairs) return;
   if (g >= n_groups) {
     pl.item_scan[g] = 0;
@@ -323,8 +325,9 @@ __global__ __launch_bounds__(kThreads) void k_items_emit(Plan pl, PlanArgs a,
   const int64_t wave0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   const int64_t n_waves = ((int64_t)gridDim.x * kThreads) >> 6;
   const int lane = threadIdx.x & 63;
-  const int32_t n_groups = (int32_t)(totals[kTotDocs] >> 32);
-  if (wave0 == 0 && lane == 0 && totals[kTotItems] > pl.items_cap)
+  const int32_t n_groups = plan_groups(totals, a.rows_cap);
+  if (wave0 == 0 && lane == 0 &&
+      (totals[kTotRows] > a.rows_cap || totals[kTotItems] > pl.items_cap))
     raise_status(a.status, DOPR_ERR_SEQLEN);
   for (int64_t gw = wave0; gw < n_groups; gw += n_waves) {
     const int32_t g = (int32_t)gw;
@@ -353,10 +356,10 @@ __global__ __launch_bounds__(kThreads) void k_items_emit(Plan pl, PlanArgs a,
 
 // Step 5c: owner of the first row of every 32-row block, so a row finds
 // its pair with one lookup and a short forward scan.
-__global__ __launch_bounds__(kThreads) void k_blk_pair(Plan pl,
+__global__ __launch_bounds__(kThreads) void k_blk_pair(Plan pl, PlanArgs a,
                                                        const int64_t *totals) {
   const int32_t s = blockIdx.x * kThreads + threadIdx.x;
-  const int32_t n_valid = (int32_t)(totals[kTotDocs] & 0xffffffff);
+  const int32_t n_valid = plan_pairs(totals, a.rows_cap);
   if (s >= n_valid) return;
   int64_t b0 = (pl.prow[s] + 31) >> 5, b1 = (pl.prow[s + 1] + 31) >> 5;
   if (b1 > pl.blk_cap) b1 = pl.blk_cap;
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(kThreads) void k_blk_pair(Plan pl,
 __global__ __launch_bounds__(kThreads) void k_token_table(Plan pl, PlanArgs a,
                                                           const int64_t *totals) {
   const int32_t s = blockIdx.x;
-  const int32_t n_valid = (int32_t)(totals[kTotDocs] & 0xffffffff);
+  const int32_t n_valid = plan_pairs(totals, a.rows_cap);
   if (s > n_valid) return;
   if (s == n_valid) {
     if (threadIdx.x == 0)
@@ -595,7 +598,9 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
   PlanArgs pa{a->doc_ids,        a->cu_seqlens,      c.st->d_len,
               c.st->n_docs,      a->total_tokens,    a->n_pairs,
               c.n_rep,           a->max_tokens,      shape.rows_per_item,
-              c.st->d_status,    shape.score_only, shape.stream};
+              c.st->d_status,    shape.score_only, shape.stream,
+              (shape.score_only ? (int64_t)shape.n_pairs
+                                : shape.total_tokens) * shape.n_rep};
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -645,7 +650,7 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                      dim3(std::min(blocks_for(P * 64, kThreads), 65536u)),
                      dim3(kThreads), 0, s, pl, pa, totals);
   hipLaunchKernelGGL(k_blk_pair, dim3(blocks_for(P, kThreads)),
-                     dim3(kThreads), 0, s, pl, totals);
+                     dim3(kThreads), 0, s, pl, pa, totals);
   if (a->cu_seqlens)
     hipLaunchKernelGGL(k_token_table, dim3((unsigned)(P + 1)),
                        dim3(kThreads), 0, s, pl, pa, totals);

@@ -236,7 +236,19 @@ struct PlanArgs {
   int32_t *status;
   bool score_only;
   bool exact_items;
+  int64_t rows_cap;  // stacked rows the plan's tables hold
 };
+
+// Groups and valid pairs of a batch, from its totals.  Token ranges that
+// follow one another stack at most rows_cap rows; with a malformed range among
+// them they may overlap and stack more, and such a batch is not run: none.
+__device__ inline int32_t plan_groups(const int64_t *totals, int64_t rows_cap) {
+  return totals[kTotRows] > rows_cap ? 0 : (int32_t)(totals[kTotDocs] >> 32);
+}
+__device__ inline int32_t plan_pairs(const int64_t *totals, int64_t rows_cap) {
+  return totals[kTotRows] > rows_cap
+             ? 0 : (int32_t)(totals[kTotDocs] & 0xffffffff);
+}
 
 // The longest-first cost class of a document group: kCostBuckets - 1 -
 // floor(log2(stacked rows * (prefix slots + 32))), clamped to the buckets

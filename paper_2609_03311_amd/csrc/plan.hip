@@ -54,7 +54,7 @@ struct OneArgs {
   PlanArgs a;
   int64_t *totals;
   int32_t *next;
-  int64_t lpt_units, rows_cap;
+  int64_t lpt_units;
   int32_t hkv, key_bits;
   // rotary table and norm bounds
   double log_theta;
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kOneThreads) void k_plan_one(OneArgs A) {
                 (unsigned long long)sm.tok[order[s]] *
                     (unsigned long long)a.n_rep);
     __syncthreads();
-    fits = sm.row_sum <= A.rows_cap;
+    fits = sm.row_sum <= a.rows_cap;
   }
   // (the scans' barriers: every thread has read its keys)
   uint32_t *row_of = sm.key;
@@ -426,8 +426,7 @@ __device__ __forceinline__ void khat_pair(const KhatParams &P, int4 sp, int L,
 template <int D>
 __global__ __launch_bounds__(kFillThreads) void k_own_khat(KhatParams P) {
   const int s = blockIdx.x;
-  const int n_valid = (int)(P.totals[kTotDocs] & 0xffffffff);
-  if (s >= n_valid) return;
+  if (s >= plan_pairs(P.totals, P.rows_cap)) return;
   khat_pair<D>(P, P.spair[s], P.doc_len[P.doc_ids[P.pair_order[s]]], 0, 1);
 }
 
@@ -542,8 +541,6 @@ hipError_t launch_plan_one(const AttnCall &c, const Plan &pl,
   o.totals = plan_totals(pl);
   o.next = plan_next(pl);
   o.lpt_units = lpt_units;
-  o.rows_cap = (shape.score_only ? (int64_t)shape.n_pairs
-                                 : shape.total_tokens) * shape.n_rep;
   o.hkv = c.st->n_kv_heads;
   o.key_bits = 0;
   while (o.key_bits < 31 && (c.st->n_docs >> o.key_bits) > 0) ++o.key_bits;

@@ -84,3 +84,35 @@ def test_overlapping_token_ranges_are_refused():
     case.step.out.fill_(7.0)
     assert _attend(case) == DOPR_ERR_SEQLEN
     assert bool((case.step.out == 7.0).all())
+
+
+@pytest.mark.parametrize("variant", [8, 6, 4])
+def test_overlapping_token_ranges_are_refused_past_the_limit(variant):
+    """The same of the general scheduler: rows beyond its tables are found
+    before any table is written from them.  A batch whose malformed range
+    leaves room is still run, that pair excepted."""
+    import torch
+    from paper_2609_03311_amd import DOPR_ERR_SEQLEN, pipeline
+    n = LIMIT + 8
+    st = workloads.custom(np.array([8, 3], np.int32),
+                          np.arange(n, dtype=np.int32) % 2,
+                          np.ones(n, np.int32), 4, 2)
+    case = setup(st, seed=5, kernel_variant=variant)
+    step = pipeline.OnlineStep(case.store, n_pairs=n, n_q_heads=4,
+                               total_tokens=n, max_tokens=100,
+                               kernel_variant=variant, with_lse=True)
+    case.step = step
+    good = case.cu
+    case.cu = (torch.arange(n + 1, dtype=torch.int32, device="cuda") % 2) * 100
+    step.out.fill_(7.0)
+    assert _attend(case) == DOPR_ERR_SEQLEN
+    assert bool((step.out == 7.0).all())
+    case.cu = good.clone()
+    case.cu[n - 1] = n + 5  # the pairs on its two sides are malformed
+    step.out.fill_(7.0)
+    assert _attend(case) == DOPR_ERR_SEQLEN
+    assert bool((step.out[n - 2:] == 7.0).all())
+    bad = step.out[:n - 2].clone()
+    case.cu = good
+    assert _attend(case) == 0
+    assert torch.equal(step.out[:n - 2], bad)
