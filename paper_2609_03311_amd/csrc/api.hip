@@ -100,13 +100,12 @@ dopr_status_t layout_store(const dopr_store_desc_t *d, StoreLayout *lay,
 // automatic choice takes when every prefix is at most kScoreRowsMaxLen
 // slots.
 int32_t default_rows_per_item(int32_t variant, bool score_only,
-                              int32_t max_len, int32_t n_rep) {
+                              int32_t max_len) {
   if (score_only)
     return (variant == 0 || variant == 5) && max_len <= kScoreRowsMaxLen
                ? 32
-               : 2048;
-  (void)n_rep;
-  return 2048;
+               : kBlockRows;
+  return kBlockRows;
 }
 
 // The full layer runs the pass kernel for variant 8 and, in the automatic
@@ -180,7 +179,7 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
   shape->rows_per_item =
       a->rows_per_item ? a->rows_per_item
                        : default_rows_per_item(a->kernel_variant, score_only,
-                                               st->max_len, *n_rep);
+                                               st->max_len);
   shape->stream =
       !score_only && uses_pass_kernel(a->kernel_variant, stacked * *n_rep) &&
       pass_kernel_holds(st, *n_rep);
@@ -412,7 +411,7 @@ dopr_status_t noalloc_too_large(size_t need) {
 dopr_status_t noalloc_shape(const dopr_attn_args_t *a, PlanShape *shape) {
   PlanShape block = *shape;
   block.stream = false;
-  block.rows_per_item = a->rows_per_item ? a->rows_per_item : 2048;
+  block.rows_per_item = a->rows_per_item ? a->rows_per_item : kBlockRows;
   if (a->kernel_variant == 8) {
     const int64_t rows = a->total_tokens * shape->n_rep;
     const int64_t cap = a->n_pairs + (rows + block.rows_per_item - 1) /

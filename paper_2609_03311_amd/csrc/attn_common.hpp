@@ -82,10 +82,6 @@ constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kTau = 8.0f;       // SAFE mode: lazy-rescale threshold
 constexpr float kHeadroom = 80.f;  // reference <= first max + 80 (log2)
 constexpr float kLoOk = 0x1p-90f, kHiOk = 0x1p100f;
-// Fix-up list entries: work unit index, plus this bit when the unit was not
-// computed by the fast pass (its logit bound exceeds kNoRefBound); those
-// run the bounded-reference mode first, the others the exact mode.
-constexpr int32_t kFixUnscored = 1 << 30;
 // Prefix chunks resident in LDS per head size: the one-block-per-CU shape
 // fills the CU's LDS (D = 128: 8 chunks, 256 slots; D = 64: 16 chunks),
 // the two-blocks-per-CU shape half of it (3 chunks at D = 128; at D = 64

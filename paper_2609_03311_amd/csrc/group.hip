@@ -309,6 +309,7 @@ __global__ __launch_bounds__(kThreads) void k_items_count(Plan pl, PlanArgs a,
     pl.item_scan[g] = 0;
     return;
   }
+  a = plan_cut(a, pl.kown);
   const int64_t rows = pl.prow[pl.group_ptr[g + 1]] - pl.prow[pl.group_ptr[g]];
   pl.item_scan[g] = (rows + a.rows_per_item - 1) / a.rows_per_item;
 }
@@ -326,6 +327,7 @@ __global__ __launch_bounds__(kThreads) void k_items_emit(Plan pl, PlanArgs a,
   const int64_t n_waves = ((int64_t)gridDim.x * kThreads) >> 6;
   const int lane = threadIdx.x & 63;
   const int32_t n_groups = plan_groups(totals, a.rows_cap);
+  a = plan_cut(a, pl.kown);
   if (wave0 == 0 && lane == 0 &&
       (totals[kTotRows] > a.rows_cap || totals[kTotItems] > pl.items_cap))
     raise_status(a.status, DOPR_ERR_SEQLEN);
@@ -409,7 +411,13 @@ __global__ __launch_bounds__(kThreads) void k_unit_table(
   const int64_t n_items = totals[kTotItems] < pl.items_cap
                               ? totals[kTotItems]
                               : pl.items_cap;
-  if (w >= n_items * sv.n_kv_heads) return;
+  const int64_t n_units = n_items * sv.n_kv_heads;
+  if (w >= n_units) return;
+  if (all_over(ua.c, pl.kown)) {
+    pl.fix[w] = (int32_t)w | kFixUnscored;
+    if (w == 0) pl.counters[kCntFix] = (int32_t)n_units;
+    return;
+  }
   const int4 it = pl.items[w / sv.n_kv_heads];
   write_unit(pl, sv, ua, w, it, pl.spair[it.w], (int32_t)(w % sv.n_kv_heads),
              totals);
@@ -600,7 +608,9 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
               c.n_rep,           a->max_tokens,      shape.rows_per_item,
               c.st->d_status,    shape.score_only, shape.stream,
               (shape.score_only ? (int64_t)shape.n_pairs
-                                : shape.total_tokens) * shape.n_rep};
+                                : shape.total_tokens) * shape.n_rep,
+              a->rows_per_item ? a->rows_per_item : kBlockRows,
+              unit_args(c).c};
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -642,6 +652,11 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
   }
   e = exclusive_scan(pl.prow, P + 1, pl.blk, totals + kTotRows, s);
   if (e != hipSuccess) return e;
+  const int32_t D = c.st->head_dim;
+  hipLaunchKernelGGL(k_norm_bound, dim3(1), dim3(D), 0, s,
+                     static_cast<const uint16_t *>(a->k_norm_w),
+                     static_cast<const uint16_t *>(a->q_norm_w), pl.kown,
+                     pl.unit_w);
   hipLaunchKernelGGL(k_items_count, dim3(blocks_for(P + 1, kThreads)),
                      dim3(kThreads), 0, s, pl, pa, totals);
   e = exclusive_scan(pl.item_scan, P + 1, pl.blk, totals + kTotItems, s);
@@ -654,11 +669,6 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
   if (a->cu_seqlens)
     hipLaunchKernelGGL(k_token_table, dim3((unsigned)(P + 1)),
                        dim3(kThreads), 0, s, pl, pa, totals);
-  const int32_t D = c.st->head_dim;
-  hipLaunchKernelGGL(k_norm_bound, dim3(1), dim3(D), 0, s,
-                     static_cast<const uint16_t *>(a->k_norm_w),
-                     static_cast<const uint16_t *>(a->q_norm_w), pl.kown,
-                     pl.unit_w);
   hipLaunchKernelGGL(k_unit_order, dim3(1), dim3(kOrderWaves * 64), 0, s, pl,
                      c.st->n_kv_heads, lpt_units, totals);
   if (pl.units) {

@@ -42,6 +42,15 @@ constexpr int64_t kPassMinRows = 16384;
 // a block's four waves.
 constexpr int32_t kPassRows = 128;
 
+// Rows per work item of the block kernels, which walk an item in passes, unless
+// the caller sets them.
+constexpr int32_t kBlockRows = 2048;
+
+// Fix-up list entries: work unit index, plus this bit when the unit was not
+// computed by the fast pass (its logit bound exceeds kNoRefBound); those
+// run the bounded-reference mode first, the others the exact mode.
+constexpr int32_t kFixUnscored = 1 << 30;
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 __host__ __device__ inline int32_t pad8(int32_t n) { return (n + 7) & ~7; }
 
@@ -237,6 +246,8 @@ struct PlanArgs {
   bool score_only;
   bool exact_items;
   int64_t rows_cap;  // stacked rows the plan's tables hold
+  int32_t rows_over;  // the block kernels' rows per item
+  float c;            // softmax_scale * log2(e)
 };
 
 // Groups and valid pairs of a batch, from its totals.  Token ranges that
@@ -248,6 +259,26 @@ __device__ inline int32_t plan_groups(const int64_t *totals, int64_t rows_cap) {
 __device__ inline int32_t plan_pairs(const int64_t *totals, int64_t rows_cap) {
   return totals[kTotRows] > rows_cap
              ? 0 : (int32_t)(totals[kTotDocs] & 0xffffffff);
+}
+
+// Whether the gains alone put every unit of a call over the logit bound: the
+// bound of a unit's keys is at least that of its own keys, kown[0].  The pass
+// kernel then has nothing to do: the plan cuts the rows into the block kernels'
+// items, which the exact pass walks with a prefix staged once for all of an
+// item's rows, and lists every unit for it (plan_cut, list_all).  Gains five
+// times the usual, us per call with the pass kernel run for nothing and 128-row
+// items for the exact pass -> now: 6,400 pairs of 129 tokens on 256 slots
+// (32 q / 8 kv heads) 26960 -> 14370, 1,600 pairs of 65 tokens on 50 documents
+// of 512 slots 3950 -> 2550.
+__device__ inline bool all_over(float c, const float *kown) {
+  return c * kown[1] * kown[0] * 1.001f > kNoRefBound;
+}
+__device__ inline PlanArgs plan_cut(PlanArgs a, const float *kown) {
+  if (a.exact_items && all_over(a.c, kown)) {
+    a.rows_per_item = a.rows_over;
+    a.exact_items = false;
+  }
+  return a;
 }
 
 // The longest-first cost class of a document group: kCostBuckets - 1 -
@@ -333,7 +364,10 @@ struct UnitArgs {
 // Work unit w of the pass kernel: item `it`, whose first pair's record is
 // sp, for kv head g.  A unit whose logits the norm bounds cannot keep within
 // the reference-free range (kNoRefBound) is marked by its pair's sign bit
-// and left to the exact pass.
+// and left to the exact pass; its record holds one row and the first key of
+// the pair, so that the pass kernel spends one batch of keys on it.  (Stored
+// keys longer than the call's own gains allow: where the gains are over the
+// bound themselves, all_over.)
 __device__ inline void write_unit(const Plan &pl, const StoreView &sv,
                                   const UnitArgs &ua, int64_t w,
                                   const int4 &it, const int4 &sp, int32_t g,
@@ -355,18 +389,18 @@ __device__ inline void write_unit(const Plan &pl, const StoreView &sv,
     to[1] = (int32_t)((uint64_t)p >> 32);
   };
   r.u.u0 = it.y / ua.n_rep;
-  r.u.rows = (it.z - it.y) | (it.y - r.u.u0 * ua.n_rep) << 8;
+  r.u.rows = (over ? 1 : it.z - it.y) | (it.y - r.u.u0 * ua.n_rep) << 8;
   r.u.s = over ? it.w | INT32_MIN : it.w;
-  r.u.L = L;
+  r.u.L = over ? 0 : L;
   put(r.u.k, sv.payload + k_offset(blk, L, sv.n_kv_heads, ua.layer, g, D));
   put(r.u.vt, sv.payload + vt_offset(blk, L, sv.n_kv_heads, ua.layer, g, D));
   put(r.u.own_k, pl.kh + (g * ua.ntok + sp.x) * D);
   put(r.u.own_v, ua.v + ((int64_t)sp.x * sv.n_kv_heads + g) * D);
   r.u.tok0 = sp.x;
-  r.u.T = sp.y;
+  r.u.T = over ? 1 : sp.y;
   // (positions are stacked latest first: the item's latest position of its
   // first pair is at its first row)
-  r.u.jmax = sp.y - 1 - (it.y - sp.z) / ua.n_rep;
+  r.u.jmax = over ? 0 : sp.y - 1 - (it.y - sp.z) / ua.n_rep;
   r.u.g = g;
 #pragma unroll
   for (int i = 0; i < 4; ++i)

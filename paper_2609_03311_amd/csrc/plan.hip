@@ -46,6 +46,7 @@ struct OneSm {
   uint32_t wsum[2][kOneWaves];
   int64_t row_sum;
   int32_t n_skip, n_zero, n_bad;
+  float kown[2];                  // the norm bounds (full rows)
 };
 static_assert(sizeof(OneSm) <= 160 * 1024, "one CU's LDS");
 
@@ -238,6 +239,13 @@ __global__ __launch_bounds__(kOneThreads) void k_plan_one(OneArgs A) {
   if (t < 64) reinterpret_cast<int32_t *>(pl.zero)[t] = 0;
   __syncthreads();
   const int P = a.n_pairs;
+  // (the pass kernel's items follow from the norm bounds: formed here too)
+  if (a.exact_items) {  // block-uniform
+    norm_bound(A.kw, A.qw, A.D, reinterpret_cast<float *>(sm.hist), sm.kown,
+               pl.unit_w);
+    __syncthreads();
+  }
+  const int32_t rows_per_item = plan_cut(a, sm.kown).rows_per_item;
   one_load(A, sm);
   __syncthreads();
   const int n_valid = P - sm.n_skip;
@@ -314,8 +322,8 @@ __global__ __launch_bounds__(kOneThreads) void k_plan_one(OneArgs A) {
     return (i + 1 < G ? row_of[first[i + 1]] : n_rows) - row_of[first[i]];
   };
   auto group_items = [&](int i) {
-    return (group_rows(i) + (uint32_t)a.rows_per_item - 1) /
-           (uint32_t)a.rows_per_item;
+    return (group_rows(i) + (uint32_t)rows_per_item - 1) /
+           (uint32_t)rows_per_item;
   };
   uint32_t items = 0;
   for (int i = g0; i < g1; ++i) items += group_items(i);
@@ -358,6 +366,8 @@ __global__ __launch_bounds__(kOneThreads) void k_plan_one(OneArgs A) {
     A.totals[kTotItems] = ok ? n_items : 0;
     A.totals[kTotUnits] = 0;  // (the items are in the queues' order)
     pl.counters[kCntInvalid] = sm.n_zero;
+    if (ok && a.exact_items && all_over(a.c, sm.kown))
+      pl.counters[kCntFix] = (int32_t)n_items * A.hkv;  // (k_plan_fill lists)
   }
 }
 
@@ -447,7 +457,8 @@ struct FillArgs {
 __device__ __forceinline__ void pair_items(const FillArgs &A, const int4 &sp,
                                            int s, const int64_t *totals) {
   const Plan &pl = A.pl;
-  const PlanArgs &a = A.a;
+  const PlanArgs a = plan_cut(A.a, A.pl.kown);
+  const bool over = A.k.kh && all_over(a.c, pl.kown);
   const int g = pl.tmp_order[s];
   const int64_t base = pl.prow[pl.group_ptr[g]];
   const int64_t R = pl.prow[pl.group_ptr[g + 1]] - base;
@@ -470,7 +481,10 @@ __device__ __forceinline__ void pair_items(const FillArgs &A, const int4 &sp,
     const int4 item = make_int4(
         g, (int32_t)b0, (int32_t)item_start(a, base, R, n_it, it + 1), s);
     if (h == 0) pl.items[at + it] = item;
-    if (A.k.kh)
+    if (over)
+      pl.fix[(at + it) * hkv + h] = (int32_t)((at + it) * hkv + h) |
+                                    kFixUnscored;
+    else if (A.k.kh)
       write_unit(pl, A.sv, A.u, (at + it) * hkv + h, item, sp, h, totals);
   }
 }

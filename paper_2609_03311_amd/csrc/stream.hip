@@ -472,6 +472,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   if (threadIdx.x == 0) {
     int64_t n_items = P0.totals[kTotItems];
     if (n_items > P0.items_cap) n_items = P0.items_cap;
+    // (every unit over the logit bound: the plan has listed them)
+    if (all_over(P0.c, P0.kown)) n_items = 0;
     const int n_work = (int)(n_items * P0.Hkv);
     const int32_t *qo = P0.totals[kTotUnits] ? P0.qorder : nullptr;
     sm.n_work = n_work;
@@ -608,9 +610,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       }
       if (P->lse && hf == 0) P->lse[orow] = __log2f(lt) * kLn2;
     }
-    // a unit over the logit bound was computed for nothing (rare) and is
-    // left to the exact pass, as is every unit in self-check mode, and one
-    // with a bad row: the first wave that finds one adds it
+    // a unit over the logit bound (one row of it was run) is left to the exact
+    // pass, as is every unit in self-check mode, and one with a bad row: the
+    // first wave that finds one adds it
     const int par = iu & 1;
     if (over || P->flag_all) {
       if (threadIdx.x == 0)
