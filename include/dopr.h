@@ -192,7 +192,12 @@ typedef struct {
   void *workspace;          /* dev scratch, >= dopr_prefix_attn_workspace() */
   size_t workspace_bytes;
   void *timing_begin;       /* optional hipEvent_t recorded on the stream
-                               right before the attention kernel, or NULL  */
+                               right before the attention kernel, or NULL.
+                               With the pass kernel (8) the interval holds
+                               the launch that forms k^; for up to 8,192
+                               pairs that launch also fills the plan's
+                               tables and zeroes the outputs of pairs
+                               without a document.                          */
   void *timing_end;         /* optional hipEvent_t recorded right after it,
                                or NULL (profiling of the dominant kernel)   */
   const float *rope_inv_freq; /* dev fp32 [D/2] rotation frequencies

@@ -918,10 +918,11 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   p.qorder = pl.qorder;
   p.ntok = a->total_tokens;
 
-  // (a small batch's plan has recorded the event before its k^ launch)
   const bool small = plan_is_small(shape);
   hipError_t e;
-  if (a->timing_begin && !small) {
+  // (a small batch's plan has recorded the event before the launch that forms
+  // k^, when there is one)
+  if (a->timing_begin && !(small && pl.kh)) {
     e = hipEventRecord(static_cast<hipEvent_t>(a->timing_begin), s);
     if (e != hipSuccess) return e;
   }

@@ -622,7 +622,7 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
   if (plan_is_small(shape)) {
     e = launch_plan_one(c, pl, shape, pa, lpt_units, s);
     if (e != hipSuccess || !a->cu_seqlens) return e;
-    if (a->timing_begin) {
+    if (a->timing_begin && pl.kh) {  // (k^ is formed there)
       e = hipEventRecord(static_cast<hipEvent_t>(a->timing_begin), s);
       if (e != hipSuccess) return e;
     }

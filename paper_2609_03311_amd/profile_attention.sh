@@ -24,7 +24,7 @@ if [ "$path" = score ]; then
   kern="k_score_rows<$D>"
 else
   tag=k_pass_attn
-  kern="k_own_khat<$D>|k_pass_attn<$D,"
+  kern="k_own_khat<$D>|k_plan_fill<$D>|k_pass_attn<$D,"
 fi
 args="--config $cfg --path $path --steps 3 --warmup 1 --no-cpu-baseline"
 bench="python3 bench.py $args"   # as recorded (run from the repository root)

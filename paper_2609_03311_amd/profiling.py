@@ -40,11 +40,12 @@ SOURCE_SETS = {
     + KERNEL_SOURCES,
 }
 # the attention launches of each path on the Qwen3-8B-shaped workload (head
-# size 128): k^ precompute + pass kernel (full layer); one wave per 32-row
+# size 128): k^ precompute (k_plan_fill in batches of up to 8,192 pairs, else
+# k_own_khat) + pass kernel (full layer); one wave per 32-row
 # unit (score rows, every prefix at most 512 slots).  Same at head size 64.
-ATTN_KERNEL = r"k_own_khat<128>|k_pass_attn<128,"
+ATTN_KERNEL = r"k_own_khat<128>|k_plan_fill<128>|k_pass_attn<128,"
 SCORE_KERNEL = r"k_score_rows<128>"
-ATTN_KERNEL_D64 = r"k_own_khat<64>|k_pass_attn<64,"
+ATTN_KERNEL_D64 = r"k_own_khat<64>|k_plan_fill<64>|k_pass_attn<64,"
 SCORE_KERNEL_D64 = r"k_score_rows<64>"
 CALIB_KERNEL = r"bitwise_not"
 CALIB_BYTES = 1 << 30

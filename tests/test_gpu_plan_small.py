@@ -116,3 +116,31 @@ def test_overlapping_token_ranges_are_refused_past_the_limit(variant):
     case.cu = good
     assert _attend(case) == 0
     assert torch.equal(step.out[:n - 2], bad)
+
+
+def test_timed_interval_leaves_the_plan_out():
+    """The timing events hold the attention alone: the launch that fills a small
+    batch's tables also zeroes a pair without a document, here 256 MB by one
+    block (2 ms), beside one pair of one token (microseconds)."""
+    import torch
+    st = workloads.custom(np.array([4, -1], np.int32),
+                          np.array([0, 1], np.int32),
+                          np.array([1, 1 << 17], np.int32), 8, 2)
+    case = setup(st, seed=6, kernel_variant=2)
+    o, p = case.online, case.prm
+
+    def call(**kw):
+        case.step.attention(0, case.doc_ids, case.cu, o["q"], o["k"], o["v"],
+                            p["q_norm_w"], p["k_norm_w"], **kw)
+
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in ev:
+        e.record()  # (creates the handle)
+    call()
+    ev[0].record()
+    call(timing=(ev[1].cuda_event, ev[2].cuda_event))
+    ev[3].record()
+    torch.cuda.synchronize()
+    whole, inside = ev[0].elapsed_time(ev[3]), ev[1].elapsed_time(ev[2])
+    assert inside < 0.25 * whole, (whole, inside)
+    assert bool((case.step.out[1:] == 0).all())
