@@ -101,8 +101,7 @@ constexpr int kLdsK = kKeyBlock * D;  // bf16 elements (swizzled rows)
 // assembly so that the compiler does not know them: it would make the next
 // LDS read, of the other buffer, wait for the loads in flight.  wait_vmem and
 // the barrier behind it order them.  s_nop 4 covers the wait states after the
-// writes of the base's scalar registers and of m0, where the compiler keeps
-// nothing in these kernels.
+// writes of the base's scalar registers and of m0.
 __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
                                            const Doc &doc, int r0, int h,
                                            uint16_t *dst) {
@@ -127,7 +126,7 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
                    :: "s"(lds + (wave + 4 * i) * 1024),
                       "v"(i & 1 ? odd : even),
                       "s"(base + (int64_t)i * 16 * heads * D)
-                   : "memory");
+                   : "memory", "m0");
     return;
   }
 #pragma unroll
@@ -137,7 +136,7 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                  "global_load_lds_dwordx4 %1, %2"
                  :: "s"(lds + (wave + 4 * i) * 1024), "v"(off), "s"(base)
-                 : "memory");
+                 : "memory", "m0");
   }
 }
 

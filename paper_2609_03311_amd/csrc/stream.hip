@@ -98,18 +98,18 @@ __device__ unsigned long long g_pass_phase[4][kPtSlots];
 // know it: it would make the wave's next LDS read, of the other buffer,
 // wait for the loads in flight.  batch_ready orders them.  s_nop 4 covers
 // the wait states after a vector write of the base's scalar registers and
-// after the write of m0, where the compiler keeps nothing in this kernel.
+// after the write of m0.
 __device__ __forceinline__ void dma_base(uint32_t lds, const void *base,
                                          uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                "global_load_lds_dwordx4 %1, %2"
                :: "s"(lds), "v"(off), "s"(base)
-               : "memory");
+               : "memory", "m0");
 }
 __device__ __forceinline__ void dma_lane(uint32_t lds, const void *p) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                "global_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(p)
-               : "memory");
+               : "memory", "m0");
 }
 
 // A whole chunk's share of one wave: its K blocks (1 KB apart in LDS) from
@@ -130,14 +130,14 @@ __device__ __forceinline__ void dma_chunk(uint32_t lds, const void *ka,
                  "global_load_lds_dwordx4 %5, %6"
                  :: "s"(lds), "v"(k1), "v"(k2), "s"(ka), "v"(v1), "v"(v2),
                     "s"(va), "n"(VOFF - 1024)
-                 : "memory", "scc");
+                 : "memory", "scc", "m0");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                  "global_load_lds_dwordx4 %1, %2\n\t"
                  "s_add_u32 m0, m0, %5\n\ts_nop 0\n\t"
                  "global_load_lds_dwordx4 %3, %4"
                  :: "s"(lds), "v"(k1), "s"(ka), "v"(v1), "s"(va), "n"(VOFF)
-                 : "memory", "scc");
+                 : "memory", "scc", "m0");
 }
 
 // The batch on its way is in LDS for every wave, and every wave is done with
