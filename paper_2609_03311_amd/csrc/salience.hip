@@ -101,7 +101,13 @@ constexpr int kLdsK = kKeyBlock * D;  // bf16 elements (swizzled rows)
 // assembly so that the compiler does not know them: it would make the next
 // LDS read, of the other buffer, wait for the loads in flight.  wait_vmem and
 // the barrier behind it order them.  s_nop 4 covers the wait states after the
-// writes of the base's scalar registers and of m0.
+// writes of the base's scalar registers and of m0.  A row's byte offset from
+// the block's first is kept in 32 bits, which 127 rows of up to kOffsetHeads
+// heads fit; rows of more heads (WIDE) are loaded through full addresses, in
+// kernels of their own (a branch here cost the others 0.3 to 0.9 %).
+constexpr int kOffsetHeads = 1 << 17;
+
+template <bool WIDE>
 __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
                                            const Doc &doc, int r0, int h,
                                            uint16_t *dst) {
@@ -115,6 +121,19 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
   // (computed here each time: kept, the eight offsets would take registers)
   asm volatile("" : "+v"(row));
   const uint32_t gran = ((lane & 15) ^ swz(row)) * 16;
+  if (WIDE) {
+#pragma unroll 1
+    for (int i = 0; i < kKeyBlock / 16; ++i) {
+      const uint16_t *p =
+          base + (int64_t)min(row + 16 * i, last) * heads * D +
+          ((gran ^ (i & 1 ? 64u : 0u)) >> 1);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                   "global_load_lds_dwordx4 %1, off"
+                   :: "s"(lds + (wave + 4 * i) * 1024), "v"(p)
+                   : "memory", "m0");
+    }
+    return;
+  }
   const uint32_t stride = (uint32_t)(heads * D * 2);
   if (last >= kKeyBlock - 1) {
     const uint32_t even = (uint32_t)row * stride + gran;
@@ -244,7 +263,7 @@ __device__ __forceinline__ float max16(const floatx16 &x) {
 // XCD reads one head's keys.  16 documents of 2048 tokens, 32 q / 8 kv heads:
 // 559 -> 327 us, with one head per sweep in place of two 430; 512 documents of
 // 256 tokens, 16 / 8 heads: 253 -> 221.
-template <int HR>
+template <int HR, bool WIDE>
 __global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
   __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
   const int d = P.d0 + blockIdx.y;
@@ -298,12 +317,12 @@ __global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
       for (int r = 0; r < HR; ++r) m[r] = -INFINITY;
     }
     if (h0 > 0) __syncthreads();  // the previous heads are done with ks[0]
-    stage_rows(P.k, P.hkv, doc, 0, g, ks[0]);
+    stage_rows<WIDE>(P.k, P.hkv, doc, 0, g, ks[0]);
     for (int kb = 0; kb <= rb; ++kb) {
       wait_vmem();
       __syncthreads();  // block kb staged; every wave done with the other
       if (kb < rb)
-        stage_rows(P.k, P.hkv, doc, (kb + 1) * kKeyBlock, g,
+        stage_rows<WIDE>(P.k, P.hkv, doc, (kb + 1) * kKeyBlock, g,
                    ks[(kb + 1) & 1]);
       const uint16_t *kbuf = ks[kb & 1];
       const int key0 = kb * kKeyBlock;
@@ -428,7 +447,7 @@ __global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
 // memory in the operand's layout, 32 rows per wave and keys from LDS it took
 // 448 us (16 documents of 2048 tokens, 32 q / 8 kv heads) and 257 (512 of 256,
 // 16 / 8 heads), now 427 and 220; 64-key units at three waves per SIMD 612.
-template <bool DIAG>
+template <bool DIAG, bool WIDE>
 __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
                                                const Doc &doc, int d, int rb,
                                                int kb,
@@ -462,11 +481,11 @@ __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
                   min(row0 + 32 * (rt + t) + lq, doc.n - 1)];
   };
   int buf = 0, h = 0;
-  stage_rows(P.k, P.hkv, doc, key0, 0, ks[0]);
+  stage_rows<WIDE>(P.k, P.hkv, doc, key0, 0, ks[0]);
   for (int g = 0; g < P.hkv; ++g) {
     wait_vmem();
     __syncthreads();  // the keys are staged; every wave done with the other
-    stage_rows(P.q, P.hq, doc, row0, h, ks[buf ^ 1]);
+    stage_rows<WIDE>(P.q, P.hq, doc, row0, h, ks[buf ^ 1]);
     load_l(h);
     bf16x8 kf[2][8];
 #pragma unroll
@@ -479,10 +498,10 @@ __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
 #pragma unroll
       for (int t = 0; t < 2; ++t) L[t] = Ln[t];
       if (r + 1 < P.n_rep) {
-        stage_rows(P.q, P.hq, doc, row0, h + 1, ks[buf ^ 1]);
+        stage_rows<WIDE>(P.q, P.hq, doc, row0, h + 1, ks[buf ^ 1]);
         load_l(h + 1);
       } else if (g + 1 < P.hkv) {
-        stage_rows(P.k, P.hkv, doc, key0, g + 1, ks[buf ^ 1]);
+        stage_rows<WIDE>(P.k, P.hkv, doc, key0, g + 1, ks[buf ^ 1]);
       }
       const uint16_t *qbuf = ks[buf] + rt * 32 * D;
       bf16x8 qf[8];
@@ -568,6 +587,7 @@ __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
 // kb, in runs of kUnitRun that go to the XCDs in turn (block b runs on XCD
 // b % 8): units that follow each other share their rows' q through one L2.
 constexpr int kUnitRun = 32;
+template <bool WIDE>
 __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
                                                       int32_t nb,
                                                       int32_t n_docs) {
@@ -588,9 +608,9 @@ __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
   const int kb = t - rb * (rb + 1) / 2;
   if (rb * kRowBlock >= doc.n) return;  // before any barrier
   if (kb < rb)  // block-uniform
-    mean_attn_unit<false>(P, doc, d, rb, kb, ks);
+    mean_attn_unit<false, WIDE>(P, doc, d, rb, kb, ks);
   else
-    mean_attn_unit<true>(P, doc, d, rb, kb, ks);
+    mean_attn_unit<true, WIDE>(P, doc, d, rb, kb, ks);
 }
 
 // ---------------------------------------------------------------------------
@@ -783,6 +803,17 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(TopkParams P) {
   }
 }
 
+template <bool WIDE>
+void launch_sweeps(const SalienceParams &p, int hr, dim3 g_lse, dim3 g_att,
+                   int nb, int32_t n_docs, hipStream_t s) {
+  if (hr == 2)
+    hipLaunchKernelGGL((k_row_lse<2, WIDE>), g_lse, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((k_row_lse<1, WIDE>), g_lse, dim3(256), 0, s, p);
+  hipLaunchKernelGGL(k_mean_attn<WIDE>, g_att, dim3(256), 0, s, p,
+                     (int32_t)nb, n_docs);
+}
+
 template <int PM>
 void launch_col_topp(const SalienceParams &p, dim3 grid, hipStream_t s) {
   constexpr int W = PM <= 16 ? 16 : PM <= 32 ? 8 : 4;
@@ -803,12 +834,10 @@ hipError_t launch_salience_chunk(const SalienceParams &p, int32_t n_docs,
   constexpr int kRun8 = 8 * kUnitRun;
   const dim3 g_att((unsigned)((units + kRun8 - 1) / kRun8 * kRun8));
   const dim3 g_col((p.max_len + kStrip - 1) / kStrip, n_docs);
-  if (hr == 2)
-    hipLaunchKernelGGL(k_row_lse<2>, g_lse, dim3(256), 0, s, p);
+  if (p.hq > kOffsetHeads)
+    launch_sweeps<true>(p, hr, g_lse, g_att, nb, n_docs, s);
   else
-    hipLaunchKernelGGL(k_row_lse<1>, g_lse, dim3(256), 0, s, p);
-  hipLaunchKernelGGL(k_mean_attn, g_att, dim3(256), 0, s, p, (int32_t)nb,
-                     n_docs);
+    launch_sweeps<false>(p, hr, g_lse, g_att, nb, n_docs, s);
   if (pm == 8)
     launch_col_topp<8>(p, g_col, s);
   else if (pm == 16)

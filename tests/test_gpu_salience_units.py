@@ -5,6 +5,8 @@ Tolerances as derived in test_gpu_salience."""
 import numpy as np
 import pytest
 
+import workloads
+
 from test_gpu_salience import (_free, check_doc, cpu_top_k, oracle_for,
                                run_case)
 
@@ -65,3 +67,25 @@ def test_selection_of_equal_values():
         for r, x in enumerate(rows):
             got = sel[r * k:(r + 1) * k].cpu().numpy()
             assert np.array_equal(got, cpu_top_k(x.astype(np.float32), k))
+
+
+def test_rows_of_many_heads():
+    """A token of 133,200 q heads is 34 MB, so row 126 of a block starts past
+    2^32 bytes.  Every head holds the same query, so the mean over heads is
+    one head's attention; the fp32 sum of n equal terms is within n 2^-24 of
+    n times one."""
+    import torch
+    n, hq, p = 127, 133200, 8
+    q1, k = workloads.salience_inputs([n], 1, 1, "cuda", 40, 2.0)
+    q = q1.expand(n, hq, 128).contiguous()
+    step, _, _ = run_case([n], hq, 1, p, n_select=[16], q=q, k=k)
+    ora = oracle_for(step, q1, k, p, [0])
+    tol = hq * 2.0 ** -24
+    low = np.tril(np.ones((n, n), bool))
+    a = step.attn_mean[0].cpu().numpy().astype(np.float64)[low]
+    ref = ora["attention"][0][low]
+    assert (np.abs(a - ref) <= tol * ref + 1e-12).all()
+    u, uo = step.u.cpu().numpy(), ora["u"][0]
+    assert (np.abs(u - uo) <= tol * uo + 1e-12).all()
+    del step, q
+    _free()
