@@ -28,8 +28,9 @@
 // matrix power holds near 1.8 GHz; each fragment read feeds two tiles.
 //   k_col_topp    per strip of 64 columns: each lane keeps the PM largest
 //                 values of its column in a sorted register list while four
-//                 waves stream interleaved rows; the lists are merged and
-//                 the top m averaged.
+//                 waves (sixteen where the launch has few, long columns)
+//                 stream interleaved rows; the lists are merged and the top m
+//                 averaged.
 //   k_topk        per document: radix search of the K-th largest u, then an
 //                 ordered compaction of the chosen positions.
 //
@@ -53,11 +54,22 @@ constexpr int D = kHeadDim;
 constexpr int kRowBlock = 128;   // rows per unit (4 waves x 32)
 constexpr int kKeyBlock = 128;   // keys per mean-attention unit
 constexpr int kStrip = 64;       // columns per top-p strip
-// Longest document from which a strip's columns are split over more than four
-// waves: from there the chain of loads outweighs the longer merge (one
-// document of 512 tokens, whole call: 105 -> 102 us, of 1024 135 -> 125, of
-// 2048 189 -> 166; 512 of 256 tokens, this kernel alone: 41 -> 62).
-constexpr int kToppWideLen = 512;
+// A strip's columns are split over sixteen waves instead of four where the
+// launch has few strips and long columns: then a column's chain of loads is
+// what it waits for.  With more strips the CUs are full either way, and the
+// longer merge of sixteen lists costs more than the shorter chains save; the
+// lists of more than 16 values merge too slowly for any split.  Whole call of
+// 4 q and 4 kv heads, us, four -> sixteen waves.  Lists of 8: 256 strips of 512
+// tokens 63.9 -> 60.8, of 1,000 91.4 -> 84.7, of 4,096 246 -> 207, 512 strips of
+// 2,048 200 -> 196; 1,024 strips of 512 139 -> 148, of 2,048 370 -> 385.  Lists
+// of 16: 192 strips of 1,536 tokens 119.6 -> 116.6, 256 of 4,096 259 -> 244; 256
+// of 1,000 100.2 -> 101.3, 512 of 2,048 227 -> 243.  Lists of 32 (eight waves):
+// 256 strips of 1,000 tokens 127.7 -> 131.7, of 4,096 315 -> 315.
+struct ToppWide {
+  int min_len;         // tokens from which on
+  int64_t max_strips;  // strips of the launch up to which
+};
+constexpr ToppWide kToppWide8 = {512, 512}, kToppWide16 = {1024, 256};
 
 __device__ __forceinline__ int perm(int m) {
   return ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3);
@@ -619,8 +631,7 @@ __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
 // the PM largest values of column c0 + l (descending, -1 = empty) and the
 // lists are merged through LDS at the end, half of them into the other half
 // at a time.  A wave walks its rows eight loads at a time, so the longest
-// column is a chain of n / 8W memory latencies: 16 documents of 2048 tokens
-// take 48 us with 16 waves and 67 with four.
+// column is a chain of n / 8W memory latencies (W: see ToppWide).
 template <int PM>
 __device__ __forceinline__ void insert(float (&L)[PM], float v) {
 #pragma unroll
@@ -816,11 +827,15 @@ void launch_sweeps(const SalienceParams &p, int hr, dim3 g_lse, dim3 g_att,
 
 template <int PM>
 void launch_col_topp(const SalienceParams &p, dim3 grid, hipStream_t s) {
-  constexpr int W = PM <= 16 ? 16 : PM <= 32 ? 8 : 4;
-  if (W > 4 && p.max_len >= kToppWideLen)
-    hipLaunchKernelGGL((k_col_topp<PM, W>), grid, dim3(64 * W), 0, s, p);
-  else
-    hipLaunchKernelGGL((k_col_topp<PM, 4>), grid, dim3(256), 0, s, p);
+  if constexpr (PM <= 16) {
+    constexpr ToppWide wide = PM == 8 ? kToppWide8 : kToppWide16;
+    if (p.max_len >= wide.min_len &&
+        (int64_t)grid.x * grid.y <= wide.max_strips) {
+      hipLaunchKernelGGL((k_col_topp<PM, 16>), grid, dim3(1024), 0, s, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_col_topp<PM, 4>), grid, dim3(256), 0, s, p);
 }
 
 }  // namespace

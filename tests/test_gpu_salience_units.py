@@ -43,6 +43,23 @@ def test_wide_strips_and_selection(n, p):
     _free()
 
 
+@pytest.mark.parametrize("docs,n,p", [(64, 512, 8), (65, 512, 8),
+                                      (16, 1024, 16), (17, 1024, 16),
+                                      (16, 1023, 16), (3, 1024, 32)])
+def test_strips_of_few_and_many_documents(docs, n, p):
+    """Both sides of the numbers of strips, and for lists of 16 of the length,
+    up to which a strip has sixteen waves."""
+    lens = [n] + [n - 1] * (docs - 2) + [5]
+    step, q, k = run_case(lens, 1, 1, p, n_select=[m // 3 for m in lens],
+                          seed=50 + docs, with_attention=False)
+    some = [0, docs // 2, docs - 2, docs - 1]
+    ora = oracle_for(step, q, k, p, some, with_attention=False)
+    for d in some:
+        check_doc(step, d, ora, with_attention=False)
+    del step
+    _free()
+
+
 def test_selection_of_equal_values():
     """All u equal, two values, infinities and zeros of both signs: the lower
     positions are taken first."""
