@@ -600,6 +600,16 @@ Plan plan_carve(void *ws, const PlanShape &s) {
   return carve(ws, s, &b);
 }
 
+hipError_t launch_rope_table(const AttnCall &c, const Plan &pl,
+                             hipStream_t s) {
+  const int32_t half = c.st->head_dim / 2;
+  hipLaunchKernelGGL(k_rope_table,
+                     dim3(blocks_for((int64_t)pl.rope_pos * half, kThreads)),
+                     dim3(kThreads), 0, s, pl.rope, pl.rope_pos, half,
+                     std::log((double)c.a->rope_theta), c.a->rope_inv_freq);
+  return hipGetLastError();
+}
+
 hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                        const PlanShape &shape, hipStream_t s) {
   const dopr_attn_args_t *a = c.a;
@@ -677,12 +687,8 @@ hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                        dim3(kThreads), 0, s, pl, c.st->view(), unit_args(c),
                        totals);
   }
-  const double log_theta = std::log((double)a->rope_theta);
-  hipLaunchKernelGGL(k_rope_table,
-                     dim3(blocks_for((int64_t)pl.rope_pos * (D / 2),
-                                     kThreads)),
-                     dim3(kThreads), 0, s, pl.rope, pl.rope_pos, D / 2,
-                     log_theta, a->rope_inv_freq);
+  e = launch_rope_table(c, pl, s);
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -464,6 +464,8 @@ struct AttnCall {
   int32_t n_rep;
   const dopr_score_head_t *head = nullptr;  // score mode (last layer)
 };
+// group.hip: the rotary table, a launch of its own.
+hipError_t launch_rope_table(const AttnCall &c, const Plan &pl, hipStream_t s);
 // plan.hip: the plan of a small batch, and (with k^ where the pass kernel
 // runs, and the zero outputs of pairs without a document) its tables.
 hipError_t launch_plan_one(const AttnCall &c, const Plan &plan,

@@ -64,6 +64,14 @@ struct OneArgs {
   int32_t D;
 };
 
+// Entries of the rotary table up to which k_plan_one's other blocks write it,
+// beside the plan.  Each of them holds the LDS of the plan's block, so one runs
+// per CU; a longer table is better written by a launch of its own.  Whole step,
+// here -> own launch, us, at 64 entries a position: 50,000 positions 46 -> 47
+// (32 pairs), 539 -> 553 (6,400); 200,000 99 -> 83, 575 -> 590; 400,000 169 ->
+// 128, 646 -> 639; 1,000,000 381 -> 276, 862 -> 785.
+constexpr int64_t kRopeInPlan = 16 << 20;
+
 // Inclusive scan over the wave: row shifts, then the rows' last lanes
 // broadcast into the rows behind them (DPP, no LDS round trips).
 __device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
@@ -564,7 +572,12 @@ hipError_t launch_plan_one(const AttnCall &c, const Plan &pl,
   o.qw = static_cast<const uint16_t *>(a->q_norm_w);
   o.D = c.st->head_dim;
   const int64_t entries = (int64_t)pl.rope_pos * (o.D / 2);
-  const unsigned rope = (unsigned)((entries + kOneThreads - 1) / kOneThreads);
+  unsigned rope = (unsigned)((entries + kOneThreads - 1) / kOneThreads);
+  if (entries > kRopeInPlan) {
+    const hipError_t e = launch_rope_table(c, pl, s);
+    if (e != hipSuccess) return e;
+    rope = 0;
+  }
   hipLaunchKernelGGL(k_plan_one, dim3(2 + rope), dim3(kOneThreads), 0, s, o);
   return hipGetLastError();
 }

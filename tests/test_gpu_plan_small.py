@@ -144,3 +144,33 @@ def test_timed_interval_leaves_the_plan_out():
     whole, inside = ev[0].elapsed_time(ev[3]), ev[1].elapsed_time(ev[2])
     assert inside < 0.25 * whole, (whole, inside)
     assert bool((case.step.out[1:] == 0).all())
+
+
+@pytest.mark.parametrize("variant", [6, 8])
+def test_rotary_table_of_a_long_store(variant):
+    """A document of 300,000 slots in the store makes the rotary table one of a
+    launch of its own; the batch does not name it and keeps its bits."""
+    import torch
+    rng = np.random.default_rng(8)
+    ids = rng.integers(0, 3, 40).astype(np.int32)
+    toks = rng.choice([1, 17, 40], 40).astype(np.int32)
+    outs = []
+    for extra in ([], [300_000]):
+        st = workloads.custom(np.array([16, 5, 70] + extra, np.int32), ids,
+                              toks, 4, 1)
+        case = setup(st, seed=7, kernel_variant=variant)
+        if extra:  # the same prefixes as in the short store
+            case.store = case.step.store = _store_with(case, keep)
+        keep = (case.k_src, case.v_src)
+        assert _attend(case) == 0
+        outs.append((case.step.out.clone(), case.step.lse.clone()))
+    assert torch.equal(outs[0][0].view(torch.int16),
+                       outs[1][0].view(torch.int16))
+    assert torch.equal(outs[0][1], outs[1][1])
+
+
+def _store_with(case, keep):
+    from paper_2609_03311_amd import pipeline
+    for mine, theirs in zip((case.k_src, case.v_src), keep):
+        mine[:theirs.shape[0]] = theirs
+    return pipeline.make_store(case.st.doc_len, 1, case.k_src, case.v_src)
