@@ -16,7 +16,7 @@ TOKENS = [1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160]
 SLOTS = [0, 1, 7, 8, 31, 32, 33, 63, 64, 65, 96, 97, 256, 257]
 
 
-def _outputs(case, variant):
+def _outputs(case, variant, order=0):
     import torch
     from paper_2609_03311_amd import pipeline
     st, o, p = case.st, case.online, case.prm
@@ -24,7 +24,8 @@ def _outputs(case, variant):
                                n_q_heads=st.n_q_heads,
                                total_tokens=st.n_tokens,
                                max_tokens=int(st.seqlens.max()),
-                               kernel_variant=variant, with_lse=True)
+                               kernel_variant=variant, with_lse=True,
+                               queue_order=order)
     step.out.fill_(float("nan"))
     step.attention(0, case.doc_ids, case.cu, o["q"], o["k"], o["v"],
                    p["q_norm_w"], p["k_norm_w"])
@@ -133,3 +134,26 @@ def test_groups_of_many_heads(n_rep):
         out, lse = _outputs(case, v)
         assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
         assert torch.equal(lse, lse2)
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("rounds,extra", [(0, 1), (0, 9), (1, -1), (1, 0),
+                                          (1, 1), (3, -1), (3, 0), (3, 1),
+                                          (4, 5)])
+def test_units_dealt_out(rounds, extra, order):
+    """As many units as the launch has blocks (two per CU, in multiples of
+    eight), times the three rounds that are dealt out, and next to that: every
+    unit is run once, in the queues' own order and longest first."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = rounds * 2 * ((cus + 7) // 8 * 8) + extra
+    rng = np.random.default_rng(n)
+    st = workloads.custom(rng.integers(0, 40, n).astype(np.int32),
+                          rng.permutation(n).astype(np.int32),
+                          rng.integers(1, 4, n).astype(np.int32), 1, 1,
+                          name=f"dealt_{n}")
+    case = setup(st, seed=13, kernel_variant=8)
+    out2, lse2 = _outputs(case, 2)
+    out, lse = _outputs(case, 8, order)
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+    assert torch.equal(lse, lse2)
