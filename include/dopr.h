@@ -153,9 +153,9 @@ typedef struct {
   int32_t n_pairs;          /* P >= 0                                       */
   int32_t n_q_heads;        /* Hq, multiple of the store's Hkv              */
   int32_t max_tokens;       /* upper bound on every T_p (>= 1)              */
-  int32_t kernel_variant;   /* 0 = automatic: 8 from 16,384 stacked rows
-                               (tokens * Hq / Hkv) on, else 6 when every
-                               prefix is resident in it and 2 when not;
+  int32_t kernel_variant;   /* 0 = automatic: 8, except at D = 64 for at most
+                               128 stacked rows (tokens * Hq / Hkv) with a
+                               prefix of more than 256 slots, which run 2;
                                1, 2, 3, 6, 8 select a
                                kernel (identical results; for tuning
                                sweeps): 1 = 4 waves x 64 rows, 2 = 8 waves

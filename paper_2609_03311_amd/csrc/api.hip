@@ -109,11 +109,13 @@ int32_t default_rows_per_item(int32_t variant, bool score_only,
 }
 
 // The full layer runs the pass kernel for variant 8 and, in the automatic
-// choice and the self-check mode, unless the batch is small (kPassMinRows).
-// Its plan then holds k^ of every token.
-bool uses_pass_kernel(int32_t variant, int64_t rows) {
-  return variant == 8 ||
-         ((variant == 0 || variant == 5) && rows >= kPassMinRows);
+// choice and the self-check mode, unless the batch is one of a few rows on long
+// prefixes at head size 64 (kOneTileSlots).  Its plan then holds k^ of every
+// token.
+bool uses_pass_kernel(int32_t variant, const dopr_store *st, int64_t rows) {
+  if (variant != 0 && variant != 5) return variant == 8;
+  return st->head_dim != 64 || rows > kPassRows ||
+         st->max_len <= kOneTileSlots;
 }
 
 // Shapes that the pass kernel's 32-bit arithmetic holds; the block kernels
@@ -181,7 +183,8 @@ dopr_status_t check_attn(const dopr_store *st, const dopr_attn_args_t *a,
                        : default_rows_per_item(a->kernel_variant, score_only,
                                                st->max_len);
   shape->stream =
-      !score_only && uses_pass_kernel(a->kernel_variant, stacked * *n_rep) &&
+      !score_only &&
+      uses_pass_kernel(a->kernel_variant, st, stacked * *n_rep) &&
       pass_kernel_holds(st, *n_rep);
   const int64_t rows = stacked * (int64_t)(*n_rep);
   const auto items_of = [&](int64_t per_item) {

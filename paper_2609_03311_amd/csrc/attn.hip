@@ -938,8 +938,8 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   // 7) unless some prefix is longer than kScoreRowsMaxLen (each 32-row unit
   // streams its whole prefix, so long prefixes shared by many pairs are
   // cheaper staged once per item by shape 6).  For full rows the pass kernel
-  // (shape 8) when the plan holds k^ of every token (a batch of at least
-  // kPassMinRows stacked rows with a workspace); without that buffer two
+  // (shape 8) when the plan holds k^ of every token; without that buffer (a
+  // call without a workspace, or one uses_pass_kernel leaves out) two
   // 4-wave blocks per CU (half the LDS each: 96 prefix slots resident at
   // D = 128, 256 at D = 64) when every prefix fits, else one 8-wave block per
   // CU with 256 (512) slots resident.  Variants 2 and 6 keep the block-wide

@@ -28,19 +28,24 @@ constexpr float kNoRefBound = 64.f;
 // own scratch array (one copy per device).
 constexpr size_t kNoAllocScratchBytes = DOPR_NOALLOC_SCRATCH_BYTES;
 
-// Stacked rows from which on the automatic choice takes the pass kernel.  In
-// a smaller batch most CUs have one work unit or none, so the call is as long
-// as its longest unit, and there the block kernels win: their prefixes are
-// resident or loaded by twice the waves, and no k^ is computed first.  Block
-// kernel -> pass kernel, us per step at head size 128: 256 to 4,096 rows 35 ->
-// 45, 40 -> 55, 46 -> 73 (prefixes of 16, 32, 250 to 500 slots); 8,192 rows
-// 55 -> 59, 65 -> 68, 76 -> 97; 16,384 rows 105 -> 94, 61 -> 63, 101 -> 75,
-// 104 -> 102; from 65,536 rows on 1071 -> 901, 1190 -> 1027, 865 -> 726.
-constexpr int64_t kPassMinRows = 16384;
-
 // Stacked rows of a work unit of the pass kernel: a 32-row tile for each of
 // a block's four waves.
 constexpr int32_t kPassRows = 128;
+
+// The automatic choice of a full layer: the pass kernel, except at head size
+// 64 for batches of at most kPassRows stacked rows with a prefix of more than
+// kOneTileSlots slots.  There a handful of units wait for their prefixes alone,
+// and a block kernel of eight waves has 512 slots of them on their way at
+// once: block kernel -> pass kernel, us per call, 1 to 104 rows 29.3 to 33.2 ->
+// 31.1 to 34.6 (500 slots), 40.2 to 49.4 -> 44.7 to 51.6 (1,500); 192 to 252
+// rows 36.2 -> 35.0 and 49.0 -> 48.3.  Elsewhere, 1 to 32 kv heads, 1 to 8 q
+// heads per kv head, 1 to 129 tokens, 8 to 1,500 slots, the pass kernel is the
+// faster one or within 5 %: head size 128, 1 to 400 rows 57 -> 54, 486 -> 330
+// (1,500 slots, one or 400 documents); 4,128 rows 87 -> 38 (head size 64, 500
+// slots); 12,000 rows 2,650 -> 1,596 (1,500 slots), 360 -> 301 (8 slots);
+// 250,000 rows 1,290 -> 1,096, 2,000 -> 1,890.  The worst of 800 batches: 82.5
+// -> 86.9 (3,500 pairs of one token on 8 slots, 2 kv heads).
+constexpr int32_t kOneTileSlots = 256;
 
 // Rows per work item of the block kernels, which walk an item in passes, unless
 // the caller sets them.

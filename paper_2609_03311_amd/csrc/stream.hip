@@ -1,6 +1,5 @@
 // stream.hip -- the pass kernel of the full online layer (the automatic
-// choice from kPassMinRows stacked rows on).  Built as
-// its own translation unit with the compiler's common-code sinking off: that
+// choice).  Built as its own translation unit with the compiler's common-code sinking off: that
 // transformation would merge stores of different unit fields into one
 // through a pointer and move wave-uniform state to scratch memory.
 #include "attn_common.hpp"

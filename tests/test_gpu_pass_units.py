@@ -86,29 +86,36 @@ def test_non_finite_values_stay_with_their_pair(d):
                        torch.nan_to_num(o2.float()))
 
 
-@pytest.mark.parametrize("tokens", [4095, 4096])
-@pytest.mark.parametrize("slots", [40, 300])
-def test_automatic_choice_on_both_sides_of_its_line(slots, tokens):
-    """16,380 and 16,384 stacked rows: the smaller batch's plan holds no own
-    keys, and both give the block kernel's bits."""
+@pytest.mark.parametrize("d,slots,tokens", [
+    (128, 40, 4095), (128, 40, 4096), (128, 300, 4095), (128, 300, 4096),
+    (128, 300, 32), (128, 8, 1), (64, 300, 33), (64, 257, 32), (64, 256, 32),
+    (64, 256, 1)])
+def test_automatic_choice_on_both_sides_of_its_line(d, slots, tokens):
+    """The pass kernel, except at head size 64 for at most 128 stacked rows
+    with a prefix of more than 256 slots: that batch's plan holds no own keys.
+    All give the block kernel's bits."""
     import torch
     import paper_2609_03311_amd as D
     lens = np.array([slots, 7, 0], np.int32)
-    toks = np.array([129] * 31 + [tokens - 31 * 129], np.int32)
-    st = workloads.custom(lens, np.arange(32) % 3, toks, 8, 2, name="line")
+    n = min(32, tokens)
+    toks = np.full(n, min(129, tokens // n), np.int32)
+    toks[-1] += tokens - toks.sum()
+    st = workloads.custom(lens, np.arange(n) % 3, toks, 8, 2, name="line",
+                          head_dim=d)
     case = setup(st, seed=11)
     assert run(case) == 0
-    compare(case, np.arange(0, 32, 5))
+    compare(case, np.arange(0, n, 5))
     out0, lse0 = _outputs(case, 0)
     out2, lse2 = _outputs(case, 2)
     assert torch.equal(out0.view(torch.int16), out2.view(torch.int16))
     assert torch.equal(lse0, lse2)
     need = [D.dopr_prefix_attn_workspace(
                 case.store, n_pairs=st.n_pairs, n_q_heads=st.n_q_heads,
-                max_tokens=129, total_tokens=tokens, kernel_variant=v)
-            for v in (0, 2)]
-    khat = 2 * tokens * 2 * 128
-    assert (need[0] >= need[1] + khat) == (tokens == 4096)
+                max_tokens=int(toks.max()), total_tokens=tokens,
+                kernel_variant=v) for v in (0, 2)]
+    khat = 2 * tokens * 2 * d
+    block = d == 64 and slots > 256 and 4 * tokens <= 128
+    assert (need[0] >= need[1] + khat) == (not block)
 
 
 @pytest.mark.parametrize("n_rep", [(1 << 15) - 1, 1 << 15, 65537])
