@@ -104,7 +104,7 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t *p) {
 // block's direct global->LDS loads overlap the products on the previous one.
 constexpr int kLdsK = kKeyBlock * D;  // bf16 elements (swizzled rows)
 
-// Rows r0 .. r0+127 of head h of the document in x [tokens, heads, D] (keys or
+// Rows r0 .. r0+ROWS-1 of head h of the document in x [tokens, heads, D] (keys or
 // queries) into `dst`: each lane writes 16 bytes of a 1 KB block (4 rows),
 // fetching the global granule that the swizzled layout puts in its slot, so
 // slot p of row r holds granule p ^ swz(r).  Rows past the document's end
@@ -119,7 +119,7 @@ constexpr int kLdsK = kKeyBlock * D;  // bf16 elements (swizzled rows)
 // kernels of their own (a branch here cost the others 0.3 to 0.9 %).
 constexpr int kOffsetHeads = 1 << 17;
 
-template <bool WIDE>
+template <bool WIDE, int ROWS = kKeyBlock>
 __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
                                            const Doc &doc, int r0, int h,
                                            uint16_t *dst) {
@@ -135,7 +135,7 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
   const uint32_t gran = ((lane & 15) ^ swz(row)) * 16;
   if (WIDE) {
 #pragma unroll 1
-    for (int i = 0; i < kKeyBlock / 16; ++i) {
+    for (int i = 0; i < ROWS / 16; ++i) {
       const uint16_t *p =
           base + (int64_t)min(row + 16 * i, last) * heads * D +
           ((gran ^ (i & 1 ? 64u : 0u)) >> 1);
@@ -147,11 +147,11 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
     return;
   }
   const uint32_t stride = (uint32_t)(heads * D * 2);
-  if (last >= kKeyBlock - 1) {
+  if (last >= ROWS - 1) {
     const uint32_t even = (uint32_t)row * stride + gran;
     const uint32_t odd = even ^ 64u;
 #pragma unroll
-    for (int i = 0; i < kKeyBlock / 16; ++i)
+    for (int i = 0; i < ROWS / 16; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                    "global_load_lds_dwordx4 %1, %2"
                    :: "s"(lds + (wave + 4 * i) * 1024),
@@ -161,7 +161,7 @@ __device__ __forceinline__ void stage_rows(const uint16_t *x, int heads,
     return;
   }
 #pragma unroll
-  for (int i = 0; i < kKeyBlock / 16; ++i) {
+  for (int i = 0; i < ROWS / 16; ++i) {
     const uint32_t off = (uint32_t)min(row + 16 * i, last) * stride +
                          (gran ^ (i & 1 ? 64u : 0u));
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
@@ -447,6 +447,30 @@ __global__ __launch_bounds__(256, 2) void k_row_lse(SalienceParams P) {
   }
 }
 
+// A tile's sums over the heads: row j's means of the keys i0 .. i0 + 15, as far
+// as the row sees them.
+__device__ __forceinline__ void store_tile(const SalienceParams &P,
+                                           const Doc &doc, int d, int j, int i0,
+                                           const floatx16 &acc) {
+  if (j >= doc.n) return;
+  float *out = P.abar + (int64_t)(d - P.d0) * P.abar_stride +
+               (int64_t)j * P.max_len;
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = acc[i] * P.inv_hq;
+  const bool vec = (P.max_len & 3) == 0;  // rows 16-byte aligned
+  if (vec && i0 + 16 <= j + 1) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      *reinterpret_cast<float4 *>(out + i0 + 4 * c) =
+          make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i0 + i <= j) out[i0 + i] = v[i];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Head-averaged attention.  Unit (rb, kb), kb <= rb, covers rows rb*128 ..
 // +127 and keys kb*128 .. +127, a 64 x 64 quarter per wave.  A wave holds its
@@ -568,31 +592,70 @@ __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
     }
     buf ^= 1;
   }
-  const bool vec = (P.max_len & 3) == 0;  // rows 16-byte aligned
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int j = row0 + 32 * (rt + t) + lq;
-    if (j >= doc.n) continue;
-    float *out = P.abar + (int64_t)(d - P.d0) * P.abar_stride +
-                 (int64_t)j * P.max_len;
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int i0 = key0 + 32 * (kt + k) + 16 * hf;
-      float v[16];
+    for (int k = 0; k < 2; ++k)
+      store_tile(P, doc, d, row0 + 32 * (rt + t) + lq,
+                 key0 + 32 * (kt + k) + 16 * hf, acc[t][k]);
+}
+
+// Documents of at most 64 tokens: three tiles, one for each of three waves, and
+// a kv head's keys and its first q head's rows share a buffer, so one wait
+// passes per q head.  The unit above has two per kv head and all three tiles on
+// one wave.  Whole call, unit above -> this one, us: 62 documents of 33 tokens,
+// 8 q and 8 kv heads 43.9 -> 33.0, 32 q and 16 kv heads 84.6 -> 54.6; 3,971
+// documents, 56 and 8 heads 2051 -> 1856; 512 of 64 tokens, 8 and 4 heads 89 ->
+// 87.  From 65 tokens on there are up to ten tiles and a second key block.
+constexpr int kShortDoc = 64;
+
+template <bool WIDE>
+__device__ __forceinline__ void mean_attn_short(const SalienceParams &P,
+                                                const Doc &doc, int d,
+                                                uint16_t (&ks)[2][kLdsK]) {
+  constexpr int Q0 = kShortDoc * D;  // the q rows' place in a buffer
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int hf = lane >> 5, lq = lane & 31;
+  const int rt = wave > 0, kt = wave > 1;  // tiles (0, 0), (1, 0), (1, 1)
+  const bool active = wave < 3 && 32 * rt < doc.n;
+  const int j = 32 * rt + lq;
+  const float *lse = P.lse2 + doc.t0 + min(j, doc.n - 1);
+  floatx16 acc;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = acc[t][k][i] * P.inv_hq;
-      if (vec && i0 + 16 <= j + 1) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          *reinterpret_cast<float4 *>(out + i0 + 4 * c) =
-              make_float4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (i0 + i <= j) out[i0 + i] = v[i];
-      }
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  bf16x8 kf[8], qf[8];
+  stage_rows<WIDE, kShortDoc>(P.k, P.hkv, doc, 0, 0, ks[0]);
+  stage_rows<WIDE, kShortDoc>(P.q, P.hq, doc, 0, 0, ks[0] + Q0);
+  float Ln = lse[0];
+  for (int h = 0, g = 0, r = 0; h < P.hq; ++h) {
+    const uint16_t *buf = ks[h & 1];
+    uint16_t *next = ks[(h & 1) ^ 1];
+    wait_vmem();
+    __syncthreads();  // head h staged; every wave done with the other buffer
+    const float L = Ln;
+    const bool first = r == 0;
+    if (++r == P.n_rep) r = 0, ++g;
+    if (h + 1 < P.hq) {
+      if (r == 0) stage_rows<WIDE, kShortDoc>(P.k, P.hkv, doc, 0, g, next);
+      stage_rows<WIDE, kShortDoc>(P.q, P.hq, doc, 0, h + 1, next + Q0);
+      Ln = lse[(int64_t)(h + 1) * P.total_tokens];
     }
+    if (!active) continue;
+    if (first) row_frags(buf, kt, perm(lq), hf, kf);
+    row_frags(buf + Q0, rt, lq, hf, qf);
+    floatx16 S;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], S, 0, 0, 0);
+    // (keys after the row are computed and not stored)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      acc[i] += __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -L));
   }
+  if (active) store_tile(P, doc, d, j, 32 * kt + 16 * hf, acc);
 }
 
 // grid: the units of each document one after another, unit rb (rb + 1) / 2 +
@@ -619,7 +682,9 @@ __global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
   while ((rb + 1) * (rb + 2) / 2 <= t) ++rb;
   const int kb = t - rb * (rb + 1) / 2;
   if (rb * kRowBlock >= doc.n) return;  // before any barrier
-  if (kb < rb)  // block-uniform
+  if (doc.n <= kShortDoc)  // block-uniform, as the next
+    mean_attn_short<WIDE>(P, doc, d, ks);
+  else if (kb < rb)
     mean_attn_unit<false, WIDE>(P, doc, d, rb, kb, ks);
   else
     mean_attn_unit<true, WIDE>(P, doc, d, rb, kb, ks);

@@ -106,3 +106,18 @@ def test_rows_of_many_heads():
     assert (np.abs(u - uo) <= tol * uo + 1e-12).all()
     del step, q
     _free()
+
+
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (2, 2), (6, 3), (6, 2), (7, 1)])
+@pytest.mark.parametrize("longest", [64, 130])
+def test_short_documents(hq, hkv, longest):
+    """Documents of up to 64 tokens take one tile per wave: lengths around its
+    tiles, alone and beside a longer document."""
+    lens = [1, 2, 31, 32, 33, 48, 63, 64, longest, 65 if longest > 64 else 7]
+    step, q, k = run_case(lens, hq, hkv, 4, n_select=[m // 2 for m in lens],
+                          seed=60 + hq)
+    ora = oracle_for(step, q, k, 4, range(len(lens)))
+    for d in range(len(lens)):
+        check_doc(step, d, ora)
+    del step
+    _free()
