@@ -600,20 +600,56 @@ __device__ __forceinline__ void mean_attn_unit(const SalienceParams &P,
                  key0 + 32 * (kt + k) + 16 * hf, acc[t][k]);
 }
 
-// Documents of at most 64 tokens: three tiles, one for each of three waves, and
-// a kv head's keys and its first q head's rows share a buffer, so one wait
-// passes per q head.  The unit above has two per kv head and all three tiles on
-// one wave.  Whole call, unit above -> this one, us: 62 documents of 33 tokens,
-// 8 q and 8 kv heads 43.9 -> 33.0, 32 q and 16 kv heads 84.6 -> 54.6; 3,971
-// documents, 56 and 8 heads 2051 -> 1856; 512 of 64 tokens, 8 and 4 heads 89 ->
-// 87.  From 65 tokens on there are up to ten tiles and a second key block.
+// grid: the units of each document one after another, unit rb (rb + 1) / 2 +
+// kb, in runs of kUnitRun that go to the XCDs in turn (block b runs on XCD
+// b % 8): units that follow each other share their rows' q through one L2.
+// Whole call in runs of 1, 4, 32 and 128 units, us: 16 documents of 2048 tokens
+// (32 q / 8 kv heads) 736, 718, 708, 805; 512 of 256 (16 / 8) 468, 458, 457, 490.
+constexpr int kUnitRun = 32;
+template <bool WIDE>
+__global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
+                                                      int32_t nb,
+                                                      int32_t n_docs) {
+  __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
+  const int slot = blockIdx.x / 8;
+  const int unit =
+      (slot / kUnitRun * 8 + blockIdx.x % 8) * kUnitRun + slot % kUnitRun;
+  const int per = nb * (nb + 1) / 2;
+  const int dd = unit / per, t = unit % per;
+  if (dd >= n_docs) return;  // block-uniform, before any barrier
+  const int d = P.d0 + dd;
+  const Doc doc = doc_at(P, d);
+  if (!doc.ok) return;
+  int rb = __builtin_amdgcn_readfirstlane(
+      (int)((sqrtf(8.f * t + 1.f) - 1.f) * 0.5f));
+  while (rb * (rb + 1) / 2 > t) --rb;
+  while ((rb + 1) * (rb + 2) / 2 <= t) ++rb;
+  const int kb = t - rb * (rb + 1) / 2;
+  if (rb * kRowBlock >= doc.n) return;  // before any barrier
+  if (kb < rb)  // block-uniform
+    mean_attn_unit<false, WIDE>(P, doc, d, rb, kb, ks);
+  else
+    mean_attn_unit<true, WIDE>(P, doc, d, rb, kb, ks);
+}
+
+// The same where no document of the call is longer than 64 tokens, a block per
+// document: three tiles, one for each of three waves, and a kv head's keys and
+// its first q head's rows share a buffer, so one wait passes per q head.  The
+// unit above has two per kv head and all three tiles on one wave.  Whole call,
+// unit above -> this kernel, us: 62 documents of 33 tokens, 8 q and 8 kv heads
+// 43.9 -> 31.7, 32 q and 16 kv heads 84.6 -> 53.1; 3,971 documents, 56 and 8
+// heads 2051 -> 1842; 512 of 64 tokens, 8 and 4 heads 89 -> 85.  From 65 tokens
+// on there are up to ten tiles and more.  (As a branch of the kernel above it
+// cost that one 1 %.)
 constexpr int kShortDoc = 64;
 
 template <bool WIDE>
-__device__ __forceinline__ void mean_attn_short(const SalienceParams &P,
-                                                const Doc &doc, int d,
-                                                uint16_t (&ks)[2][kLdsK]) {
+__global__ __launch_bounds__(256, 2) void k_mean_attn_short(SalienceParams P) {
   constexpr int Q0 = kShortDoc * D;  // the q rows' place in a buffer
+  __shared__ __attribute__((aligned(16))) uint16_t ks[2][2 * Q0];
+  const int d = P.d0 + blockIdx.x;
+  const Doc doc = doc_at(P, d);
+  if (!doc.ok) return;  // block-uniform, before any barrier
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int hf = lane >> 5, lq = lane & 31;
@@ -656,38 +692,6 @@ __device__ __forceinline__ void mean_attn_short(const SalienceParams &P,
       acc[i] += __builtin_amdgcn_exp2f(fmaf(S[i], P.c, -L));
   }
   if (active) store_tile(P, doc, d, j, 32 * kt + 16 * hf, acc);
-}
-
-// grid: the units of each document one after another, unit rb (rb + 1) / 2 +
-// kb, in runs of kUnitRun that go to the XCDs in turn (block b runs on XCD
-// b % 8): units that follow each other share their rows' q through one L2.
-constexpr int kUnitRun = 32;
-template <bool WIDE>
-__global__ __launch_bounds__(256, 2) void k_mean_attn(SalienceParams P,
-                                                      int32_t nb,
-                                                      int32_t n_docs) {
-  __shared__ __attribute__((aligned(16))) uint16_t ks[2][kLdsK];
-  const int slot = blockIdx.x / 8;
-  const int unit =
-      (slot / kUnitRun * 8 + blockIdx.x % 8) * kUnitRun + slot % kUnitRun;
-  const int per = nb * (nb + 1) / 2;
-  const int dd = unit / per, t = unit % per;
-  if (dd >= n_docs) return;  // block-uniform, before any barrier
-  const int d = P.d0 + dd;
-  const Doc doc = doc_at(P, d);
-  if (!doc.ok) return;
-  int rb = __builtin_amdgcn_readfirstlane(
-      (int)((sqrtf(8.f * t + 1.f) - 1.f) * 0.5f));
-  while (rb * (rb + 1) / 2 > t) --rb;
-  while ((rb + 1) * (rb + 2) / 2 <= t) ++rb;
-  const int kb = t - rb * (rb + 1) / 2;
-  if (rb * kRowBlock >= doc.n) return;  // before any barrier
-  if (doc.n <= kShortDoc)  // block-uniform, as the next
-    mean_attn_short<WIDE>(P, doc, d, ks);
-  else if (kb < rb)
-    mean_attn_unit<false, WIDE>(P, doc, d, rb, kb, ks);
-  else
-    mean_attn_unit<true, WIDE>(P, doc, d, rb, kb, ks);
 }
 
 // ---------------------------------------------------------------------------
@@ -886,6 +890,11 @@ void launch_sweeps(const SalienceParams &p, int hr, dim3 g_lse, dim3 g_att,
     hipLaunchKernelGGL((k_row_lse<2, WIDE>), g_lse, dim3(256), 0, s, p);
   else
     hipLaunchKernelGGL((k_row_lse<1, WIDE>), g_lse, dim3(256), 0, s, p);
+  if (p.max_len <= kShortDoc) {
+    hipLaunchKernelGGL(k_mean_attn_short<WIDE>, dim3(n_docs), dim3(256), 0, s,
+                       p);
+    return;
+  }
   hipLaunchKernelGGL(k_mean_attn<WIDE>, g_att, dim3(256), 0, s, p,
                      (int32_t)nb, n_docs);
 }
