@@ -26,7 +26,7 @@ TIMERS_BUILD = os.path.join(HERE, "_build", "timers")
 TIMERS_LIB = os.path.join(HERE, "libdopr_timers.so")
 SOURCES = ["api.hip", "store.hip", "group.hip", "plan.hip", "attn.hip",
            "stream.hip", "score.hip", "layer.hip", "salience.hip"]
-# per-file flags: the streaming kernel's cursor must stay in scalar
+# per-file flags: the pass kernel's cursor must stay in scalar
 # registers (common-code sinking would move it to scratch memory), and its
 # claims are atomics whose results are read much later (the wave-wide form
 # the compiler would make of them reads each result at once)

@@ -912,11 +912,9 @@ hipError_t launch_attention(const AttnCall &c, const Plan &pl,
   p.n_layers = st.n_layers;
   p.eps = a->rms_eps;
   p.c = a->softmax_scale * 1.4426950408889634f;
-  p.kh = pl.kh;
   p.zero = pl.zero;
   p.units = pl.units;
   p.qorder = pl.qorder;
-  p.ntok = a->total_tokens;
 
   const bool small = plan_is_small(shape);
   hipError_t e;

@@ -1,6 +1,6 @@
 // attn_common.hpp -- device building blocks shared by the attention
 // kernels (attn.hip: block kernels, last-layer scoring; stream.hip: the
-// streaming kernel): operand layouts and swizzles, the q^ and k^
+// pass kernel): operand layouts and swizzles, the q^ and k^
 // prologues, and the MFMA/softmax steps of one 32-key chunk.  Internal to
 // the library.
 #pragma once
@@ -35,11 +35,9 @@ struct AttnParams {
   const int32_t *pair_order;
   float *part;
   const uint16_t *head_norm_w, *head_w;
-  // pass kernel: precomputed own keys k^ [Hkv][Ntok][D], a zero page and
-  // the work-unit table
-  const uint16_t *kh, *zero;
+  // pass kernel: a zero page and the work-unit table
+  const uint16_t *zero;
   const PassUnit *units;
-  int64_t ntok;
   // work units of each queue, costliest first (see unit_at)
   const int32_t *qorder;
   int32_t items_cap, Hq, Hkv, n_rep, layer, n_layers;
@@ -48,7 +46,7 @@ struct AttnParams {
   float eps, c;      // c = softmax_scale * log2(e)
 };
 
-// Arguments of k_own_khat (k^ of every online token, for the streaming
+// What the own keys k^ of every online token are formed from (for the pass
 // kernel).
 struct KhatParams {
   const uint16_t *k, *kw;
@@ -317,8 +315,8 @@ __device__ __forceinline__ void unpack8_at(int k, const uint4 &u,
 // + NS/GROUP - 1 and, of every k-step pair s, the rotary float4s
 // e2 = qk*4/GROUP .. + 4/GROUP - 1, so the
 // group's loads of one k-step cover contiguous bytes of the row.  In two
-// steps: the loads of a row, and q^ from the loaded row (the pass kernel
-// issues the loads one pass ahead).
+// steps, the loads of a row, and q^ from the loaded row and the gains: the pass
+// kernel takes the gains from LDS, the others from memory.
 template <int D, int GROUP>
 struct QRow {
   static constexpr int NS = D / 16, HS = NS / 2, EW = 4 / GROUP;

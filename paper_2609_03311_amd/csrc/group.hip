@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void k_items_count(Plan pl, PlanArgs a,
 // Step 5b: split a group's rows into items, boundaries on multiples of 32
 // rows: near-equal items (the block kernels, which walk an item in passes),
 // or, with exact_items, items of exactly rows_per_item rows and a shorter
-// last one (the streaming kernel serves an item in one pass, so no item
+// last one (the pass kernel serves an item in one pass, so no item
 // may exceed it).  One wave per group, its lanes taking the items in turn:
 // a hot document's group has hundreds of items, each with its own search.
 // The waves stride over the groups, so the grid stays bounded.
@@ -419,8 +419,7 @@ __global__ __launch_bounds__(kThreads) void k_unit_table(
     return;
   }
   const int4 it = pl.items[w / sv.n_kv_heads];
-  write_unit(pl, sv, ua, w, it, pl.spair[it.w], (int32_t)(w % sv.n_kv_heads),
-             totals);
+  write_unit(pl, sv, ua, w, it, pl.spair[it.w], (int32_t)(w % sv.n_kv_heads));
 }
 
 // Step 5f: the longest-first order of the work-unit queues.  Unit w =

@@ -235,7 +235,7 @@ struct Plan {
   float2 *rope;         // [rope_pos][D/2] (cos, sin)
   uint16_t *kh;         // [Hkv][Ntok][D] own keys k^ (pass kernel), or NULL
   PassUnit *units;      // [items_cap * Hkv] work units (pass kernel)
-  uint16_t *zero;       // 256 zero bytes (streaming kernel loads past row ends)
+  uint16_t *zero;       // 256 zero bytes (the pass kernel loads them past row ends)
   int32_t items_cap;
   int32_t blk_cap;
   int32_t rope_pos;
@@ -375,8 +375,7 @@ struct UnitArgs {
 // bound themselves, all_over.)
 __device__ inline void write_unit(const Plan &pl, const StoreView &sv,
                                   const UnitArgs &ua, int64_t w,
-                                  const int4 &it, const int4 &sp, int32_t g,
-                                  const int64_t *totals) {
+                                  const int4 &it, const int4 &sp, int32_t g) {
   const int D = sv.head_dim;
   const int32_t doc = pl.group_doc[it.x];
   const int32_t L = sv.doc_len[doc];

@@ -463,7 +463,7 @@ struct FillArgs {
 // their work units: the pair is then the item's first one, and a document
 // with hundreds of items is spread over its pairs' blocks.
 __device__ __forceinline__ void pair_items(const FillArgs &A, const int4 &sp,
-                                           int s, const int64_t *totals) {
+                                           int s) {
   const Plan &pl = A.pl;
   const PlanArgs a = plan_cut(A.a, A.pl.kown);
   const bool over = A.k.kh && all_over(a.c, pl.kown);
@@ -493,7 +493,7 @@ __device__ __forceinline__ void pair_items(const FillArgs &A, const int4 &sp,
       pl.fix[(at + it) * hkv + h] = (int32_t)((at + it) * hkv + h) |
                                     kFixUnscored;
     else if (A.k.kh)
-      write_unit(pl, A.sv, A.u, (at + it) * hkv + h, item, sp, h, totals);
+      write_unit(pl, A.sv, A.u, (at + it) * hkv + h, item, sp, h);
   }
 }
 
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kFillThreads) void k_plan_fill(FillArgs A) {
          b += kFillThreads)
       pl.blk_pair[b] = s;
   }
-  if (part == 0) pair_items(A, sp, s, totals);
+  if (part == 0) pair_items(A, sp, s);
   if (A.k.kh)
     khat_pair<D>(A.k, sp, a.doc_len[a.doc_ids[p]], part, A.parts);
 }
