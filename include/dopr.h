@@ -169,7 +169,10 @@ typedef struct {
                                stream their keys through LDS and read the
                                own keys from a k^ buffer in the workspace
                                (2 Hkv D bytes per online token) filled by a
-                               separate normalise-and-rotate kernel;
+                               separate normalise-and-rotate kernel (block
+                               kernels run in its place from 2^15 q heads
+                               per kv head, prefixes of 2^31 / D slots or
+                               Hkv D = 2^25 on);
                                4 = exact running-max softmax for every row
                                (slower; the reference for the fast path);
                                5 = self-check: the fast pass queues every

@@ -17,9 +17,10 @@ kernel that reads and writes exactly `CALIB_BYTES`.  `pmc` condenses
 fractions per kernel.  Every summary records a hash of the kernels' sources
 so a reader can tell whether the figures still describe the code.
 
-The full layer's attention is two launches: `k_own_khat` (k^ of every
-online token) and the pass kernel `k_pass_attn`; both are timed and
-counted together as one attention step.
+The full layer's attention is two launches: the one that forms k^ of every
+online token (`k_plan_fill` up to 8,192 pairs, else `k_own_khat`) and the pass
+kernel `k_pass_attn`; both are timed and counted together as one attention
+step.
 """
 import argparse
 import csv

@@ -158,8 +158,8 @@ def test_outputs_do_not_depend_on_queue_order():
     """Units are scored independently, so the order the work queues hand
     them out in must not change a bit: natural and longest-first order
     against the automatic choice, on qwen3_4b (about 52 units per CU, where
-    the automatic choice is longest-first), for the block kernel the
-    automatic choice takes there, the pass kernel and last-layer scoring."""
+    the automatic choice is longest-first), for the pass kernel, a block
+    kernel and last-layer scoring."""
     import torch
     import paper_2609_03311_amd as D
     from paper_2609_03311_amd import pipeline
@@ -168,7 +168,7 @@ def test_outputs_do_not_depend_on_queue_order():
     assert run(case) == 0
     o, p = case.online, case.prm
     ref_out, ref_lse = case.step.out.clone(), case.step.lse.clone()
-    for variant in (0, 8):
+    for variant in (0, 8, 6):
         for order in (1, 2):
             step = pipeline.OnlineStep(
                 case.store, n_pairs=st.n_pairs, n_q_heads=st.n_q_heads,
