@@ -988,6 +988,8 @@ KhatParams khat_params(const AttnCall &c, const Plan &pl) {
   kp.spair = pl.spair;
   kp.totals = plan_totals(pl);
   kp.rope = pl.rope;
+  kp.kown = pl.kown;
+  kp.c = unit_args(c).c;
   kp.kh = pl.kh;
   kp.ntok = a->total_tokens;
   kp.rows_cap = a->total_tokens * c.n_rep;  // (full rows only)

@@ -54,8 +54,10 @@ struct KhatParams {
   const int4 *spair;
   const int64_t *totals;
   const float2 *rope;
+  const float *kown;
   uint16_t *kh;
   int64_t ntok, rows_cap;
+  float c;
   int32_t Hkv;
   float eps;
   int32_t norm;

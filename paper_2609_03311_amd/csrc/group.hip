@@ -612,19 +612,23 @@ hipError_t launch_rope_table(const AttnCall &c, const Plan &pl,
 hipError_t launch_plan(const AttnCall &c, const Plan &pl,
                        const PlanShape &shape, hipStream_t s) {
   const dopr_attn_args_t *a = c.a;
-  PlanArgs pa{a->doc_ids,        a->cu_seqlens,      c.st->d_len,
-              c.st->n_docs,      a->total_tokens,    a->n_pairs,
-              c.n_rep,           a->max_tokens,      shape.rows_per_item,
-              c.st->d_status,    shape.score_only, shape.stream,
-              (shape.score_only ? (int64_t)shape.n_pairs
-                                : shape.total_tokens) * shape.n_rep,
-              a->rows_per_item ? a->rows_per_item : kBlockRows,
-              unit_args(c).c};
   int dev = 0, n_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
+  const int64_t rows_cap =
+      (shape.score_only ? (int64_t)shape.n_pairs : shape.total_tokens) *
+      shape.n_rep;
+  PlanArgs pa{a->doc_ids,        a->cu_seqlens,      c.st->d_len,
+              c.st->n_docs,      a->total_tokens,    a->n_pairs,
+              c.n_rep,           a->max_tokens,      shape.rows_per_item,
+              c.st->d_status,    shape.score_only, shape.stream,
+              rows_cap,
+              a->rows_per_item
+                  ? a->rows_per_item
+                  : over_rows(rows_cap * shape.n_kv_heads, n_cu),
+              unit_args(c).c};
   const int64_t lpt_units = a->queue_order == 1   ? 0
                             : a->queue_order == 2 ? kOrderMaxUnits
                                                   : kLptUnitsPerCu * n_cu;

@@ -251,7 +251,7 @@ struct PlanArgs {
   bool score_only;
   bool exact_items;
   int64_t rows_cap;  // stacked rows the plan's tables hold
-  int32_t rows_over;  // the block kernels' rows per item
+  int32_t rows_over;  // rows per item where every unit is over the bound
   float c;            // softmax_scale * log2(e)
 };
 
@@ -268,15 +268,28 @@ __device__ inline int32_t plan_pairs(const int64_t *totals, int64_t rows_cap) {
 
 // Whether the gains alone put every unit of a call over the logit bound: the
 // bound of a unit's keys is at least that of its own keys, kown[0].  The pass
-// kernel then has nothing to do: the plan cuts the rows into the block kernels'
-// items, which the exact pass walks with a prefix staged once for all of an
-// item's rows, and lists every unit for it (plan_cut, list_all).  Gains five
-// times the usual, us per call with the pass kernel run for nothing and 128-row
-// items for the exact pass -> now: 6,400 pairs of 129 tokens on 256 slots
-// (32 q / 8 kv heads) 26960 -> 14370, 1,600 pairs of 65 tokens on 50 documents
-// of 512 slots 3950 -> 2550.
+// kernel then has nothing to do: the plan cuts the rows into items for the
+// exact pass, which walks an item with a prefix staged once for all of its
+// rows, lists every unit for it (plan_cut) and leaves k^ out (6,400 pairs of 129
+// tokens on 256 slots, 32 q / 8 kv heads: 13780 -> 13110 us).
 __device__ inline bool all_over(float c, const float *kown) {
   return c * kown[1] * kown[0] * 1.001f > kNoRefBound;
+}
+// Rows of those items (rows: stacked rows times kv heads): the block kernels'
+// size in a large batch, less where the CUs would not get kOverUnitsPerCu units
+// each, down to one pass of the exact kernel.  Gains five times the usual, us
+// per call (k^ formed) with items of 128, 512 and 2,048 rows: 6,400 pairs of 129 tokens on
+// 256 slots (32 q / 8 kv heads) 18230, 14840, 13780; 1,600 of 65 on 50 documents
+// of 512 slots 2700, 2650, 2750; 100 of 129 on 256 slots 320, 280, 290.  Six
+// times, where many a row takes the exact mode and its unit with it: 30,000 rows
+// of 27 documents of 1,500 slots, one kv head, 170 (2,048 rows: 1,460);
+// 59 pairs of 129 tokens on one document, 2 kv heads, 92 (460).
+constexpr int32_t kOverUnitsPerCu = 8;
+inline int32_t over_rows(int64_t rows, int n_cu) {
+  const int64_t per = rows / ((int64_t)kOverUnitsPerCu * n_cu) / kPassRows;
+  return per < 1 ? kPassRows
+         : per >= kBlockRows / kPassRows ? kBlockRows
+                                         : (int32_t)per * kPassRows;
 }
 __device__ inline PlanArgs plan_cut(PlanArgs a, const float *kown) {
   if (a.exact_items && all_over(a.c, kown)) {

@@ -440,11 +440,11 @@ __device__ __forceinline__ void khat_pair(const KhatParams &P, int4 sp, int L,
 }
 
 // The same for every sorted pair of a batch the general scheduler planned,
-// one block per pair.
+// one block per pair; for none where the pass kernel has nothing to do.
 template <int D>
 __global__ __launch_bounds__(kFillThreads) void k_own_khat(KhatParams P) {
   const int s = blockIdx.x;
-  if (s >= plan_pairs(P.totals, P.rows_cap)) return;
+  if (s >= plan_pairs(P.totals, P.rows_cap) || all_over(P.c, P.kown)) return;
   khat_pair<D>(P, P.spair[s], P.doc_len[P.doc_ids[P.pair_order[s]]], 0, 1);
 }
 
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(kFillThreads) void k_plan_fill(FillArgs A) {
       pl.blk_pair[b] = s;
   }
   if (part == 0) pair_items(A, sp, s);
-  if (A.k.kh)
+  if (A.k.kh && !all_over(a.c, pl.kown))
     khat_pair<D>(A.k, sp, a.doc_len[a.doc_ids[p]], part, A.parts);
 }
 
