@@ -157,8 +157,11 @@ typedef struct {
                                128 stacked rows (tokens * Hq / Hkv) with a
                                prefix of more than 256 slots, which run 2;
                                1, 2, 3, 6, 8 select a
-                               kernel (identical results; for tuning
-                               sweeps): 1 = 4 waves x 64 rows, 2 = 8 waves
+                               kernel (identical results, except that a
+                               unit over the logit bound with a row out of
+                               range is recomputed whole by the exact pass,
+                               to bf16 rounding, and units differ; for
+                               tuning sweeps): 1 = 4 waves x 64 rows, 2 = 8 waves
                                x 32 rows, 3 = 4 waves x 32 rows (each one
                                block per CU, 256 prefix slots resident;
                                512 at D = 64), 6 = 4 waves x 32 rows, two
@@ -211,7 +214,9 @@ typedef struct {
                                work items a document's rows are cut into:
                                a multiple of 32 in [64, 2^20] (the pass
                                kernel's items hold at most 128).  Outputs do
-                               not depend on it (a tuning and test knob).
+                               not depend on it, but for the rounding of
+                               units recomputed whole (see kernel_variant;
+                               a tuning and test knob).
                                Full-row calls only: must be 0 for
                                dopr_prefix_attn_score (INVALID_ARG).        */
   int32_t queue_order;      /* order in which each of the 8 work queues
